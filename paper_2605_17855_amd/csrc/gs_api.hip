@@ -176,8 +176,7 @@ Workspace carve(void *ws, int64_t n, uint64_t capacity) {
 // sees its rows in the same order with the same arithmetic, so the image does not depend on
 // the split.
 int raster_parts(const gs_options &o) {
-  if (o.precision == GS_PREC_FP32) return 1;
-  if (o.group == 2 && !(o.flags & GS_OPT_TILE_ROWS)) return 2;   // the group-frame rows
+  if (o.precision != GS_PREC_FP32 && o.group == 2 && !(o.flags & GS_OPT_TILE_ROWS)) return 2;   // the group-frame rows
   return o.group * o.group;
 }
 

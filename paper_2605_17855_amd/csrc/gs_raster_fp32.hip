@@ -1,148 +1,254 @@
 // Plain FP32 rasterizer (paper, Background: tile-based rasterization, eq. power_d, eq. power).
 //
-// One 256-lane workgroup per bin (a tile, or a GxG tile group); each lane owns one pixel
-// position and, for a group, that position in every member tile.  The bin's depth-sorted
+// One 256-lane workgroup per tile; lane = pixel, wave = 8x8 quadrant.  The tile's depth-sorted
 // list is streamed through LDS in chunks of 256 entries.  Per (entry, pixel):
 //   d = x - mu'                       (eq. power_d)
 //   log2(alpha_raw) = log2(o) + log2(e) * (-1/2 d^T conic d)   (eq. power)
 //   skip when alpha_raw < 1/255, alpha = min(0.99, alpha_raw)
 //   T' = T (1 - alpha); stop (without blending) when T' < 1e-4; else C += alpha T c, T = T'.
-// The pixel's offset to the centre is formed from a group-relative FP32 copy of the FP64
-// centre, so |d| stays small and exact.  Lanes map to 8x8 quadrants per wave so that a
-// splat that misses a quadrant is skipped by the whole wave.
-#include "gs_internal.hpp"
+// The pixel's offset to the centre is formed from a bin-relative FP32 copy of the FP64
+// centre, so |d| stays small and exact.
+//
+// Each wave walks only the rows whose alpha can reach the 1/255 cut in its own quadrant (the
+// quadrant mask of the tensorized rasterizer, its margin far above this test's and the FP32
+// power's rounding, so no output changes).  A row's nine floats are LDS reads broadcast to 64
+// pixels, ~20 LDS cycles per wave and row at 128 B per cycle, and four SIMDs share one LDS:
+// running every row in every quadrant was bound by exactly that (6.3M wave-rows of a 1M-Gaussian
+// 1080p frame, 242 us).  The lists keep about a third of them.
+//
+// Tile groups (G > 1): one workgroup per member tile, walking the group's list and keeping the
+// entries whose mask holds its tile, in list order, in a row buffer that fills over several
+// steps (the member-tile rasterizer of gs_raster_mfma.hip); centres stay relative to the group.
+#include "gs_mfma.hpp"
 
 namespace gsi {
 namespace {
 
-
+template <int CAP_>
 struct Fp32Shared {
-  float4 a[kBlock];  // (u, v, -a/2 log2e, -b log2e)
-  float4 b[kBlock];  // (-c/2 log2e, log2 o, r, g)
-  float4 c[kBlock];  // (b, mask bits, -, -)
+  static constexpr int CAP = CAP_;
+  float4 a[CAP + 1];     // (u, v, -a/2 log2e, -b log2e); row CAP never passes the cut
+  float4 b[CAP + 1];     // (-c/2 log2e, log2 o, r, g)
+  float c[CAP + 1];      // b
+  uint32_t alive[2][4];
+  __align__(16) uint32_t wcnt[2][4];   // groups: the tile's entries per wave in a step, by step parity
+  uint8_t qm[CAP];       // quadrant masks
+  uint16_t wl[4][CAP];   // each wave's row list
 };
 
-// Renders bin `bin` of job J (one workgroup; this rasterizer takes one work item per bin).
-// Shared by the single-image and batched kernels.
-template <int G, bool AUX>
-__device__ __forceinline__ void raster_bin_fp32(const RasterJob &J, const RasterParams &P, int bin, Fp32Shared &sm) {
-  constexpr int NT = G * G;
-  const int gx = bin % J.GX, gy = bin / J.GX;
-  const int ox = gx * G * kTile, oy = gy * G * kTile;
-  const uint32_t start = J.ranges[2 * bin], end = J.ranges[2 * bin + 1];
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  const int px = (w & 1) * 8 + (lane & 7), py = (w >> 1) * 8 + (lane >> 3);
+struct PixelState {
+  float T, C0, C1, C2, W, cut;
+  uint32_t nstop, nblend, last;   // last: 1 + list position of the last Gaussian blended
+};
 
-  float T[NT], C0[NT], C1[NT], C2[NT], Ws[NT], cut[NT];
-  uint32_t nstop[NT], nseen[NT], nblend[NT], nlast[NT];
-  float X[NT], Y[NT];
+// Runs the rows wl[0, n) (ascending buffer indices) for this lane's pixel (X, Y).  Rows go in
+// blocks of four, all their LDS reads and powers ahead of the blends.  row_base: list position
+// of buffer row 0.
+template <bool AUX, typename SM>
+__device__ __forceinline__ void blend_rows(const SM &sm, const uint16_t *wl, int n, float X, float Y, PixelState &st,
+                                           uint32_t row_base) {
+  constexpr int U = 4;
+  const int lane = threadIdx.x & 63;
+  for (int r0 = 0; r0 < n; r0 += 64) {
+    // a wave whose pixels have all stopped leaves its list
+    if (__ballot(st.cut != INFINITY) == 0) return;
+    const int idx = r0 + lane < n ? (int)wl[r0 + lane] : SM::CAP;
+    const int m = min(64, n - r0);
+    for (int k = 0; k < m; k += U) {
+      float D[U];
+      float4 B[U];
+      float c2[U];
+      int ri[U];
 #pragma unroll
-  for (int k = 0; k < NT; ++k) {
-    const int lx = (k % G) * kTile + px, ly = (k / G) * kTile + py;
-    X[k] = lx + 0.5f;
-    Y[k] = ly + 0.5f;
-    const bool inside = (ox + lx < J.W) && (oy + ly < J.H);
-    T[k] = 1.0f; C0[k] = C1[k] = C2[k] = 0.0f; Ws[k] = 0.0f;
-    cut[k] = inside ? kCutLog2 : INFINITY;
-    nstop[k] = 0; nseen[k] = 0; nblend[k] = 0; nlast[k] = 0;
-  }
-
-  for (uint32_t cs = start; cs < end; cs += kBlock) {
-    const int cnt = (int)min((uint32_t)kBlock, end - cs);
-    __syncthreads();
-    if (t < cnt) {
-      const uint32_t e = cs + t;
-      const uint32_t g = J.vals[e];
-      const double2 m = J.xy[g];
-      const float4 co = J.conic[g];
-      const float4 cl = J.rgb[g];
-      const uint32_t mk = (G > 1) ? (uint32_t) static_cast<const uint16_t *>(J.masks)[e] : 1u;
-      sm.a[t] = make_float4((float)(m.x - ox), (float)(m.y - oy), -0.5f * kLog2e * co.x, -kLog2e * co.y);
-      sm.b[t] = make_float4(-0.5f * kLog2e * co.z, __log2f(co.w), cl.x, cl.y);
-      sm.c[t] = make_float4(cl.z, __uint_as_float(mk), 0.0f, 0.0f);
-    }
-    bool alive = false;
-#pragma unroll
-    for (int k = 0; k < NT; ++k) alive |= cut[k] != INFINITY;
-    if (!__syncthreads_or(alive)) break;
-    for (int j = 0; j < cnt; ++j) {
-      if ((j & 31) == 0) {
-        // a wave whose pixels have all stopped leaves the chunk early
-        bool any = false;
-#pragma unroll
-        for (int k = 0; k < NT; ++k) any |= cut[k] != INFINITY;
-        if (__ballot(any) == 0) break;
+      for (int j = 0; j < U; ++j) {
+        ri[j] = __builtin_amdgcn_readlane(idx, k + j);
+        const float4 A = sm.a[ri[j]];
+        B[j] = sm.b[ri[j]];
+        c2[j] = sm.c[ri[j]];
+        const float dx = X - A.x, dy = Y - A.y;
+        D[j] = fmaf(dx, fmaf(A.z, dx, A.w * dy), fmaf(B[j].x * dy, dy, B[j].y));
       }
-      const float4 A = sm.a[j];
-      const float4 B = sm.b[j];
-      const float4 Cc = sm.c[j];
-      const uint32_t mk = __float_as_uint(Cc.y);
 #pragma unroll
-      for (int k = 0; k < NT; ++k) {
-        if (G > 1 && !((mk >> k) & 1u)) continue;
-        if (AUX) nseen[k]++;
-        const float dx = X[k] - A.x, dy = Y[k] - A.y;
-        const float D = fmaf(dx, fmaf(A.z, dx, A.w * dy), fmaf(B.x * dy, dy, B.y));
-        if (D >= cut[k]) {
+      for (int j = 0; j < U; ++j) {
+        if (D[j] >= st.cut) {
           // branch-free body: T' = T (1 - alpha) as one FMA; a stop (T' < 1e-4) blends
           // nothing, keeps T and disables the pixel
-          const float al = fminf(kAlphaMax, __builtin_amdgcn_exp2f(D));
-          const float Tn = fmaf(-T[k], al, T[k]);
+          const float al = fminf(kAlphaMax, __builtin_amdgcn_exp2f(D[j]));
+          const float Tn = fmaf(-st.T, al, st.T);
           const bool ok = Tn >= kTMin;
-          const float wgt = ok ? al * T[k] : 0.0f;
-          C0[k] = fmaf(wgt, B.z, C0[k]);
-          C1[k] = fmaf(wgt, B.w, C1[k]);
-          C2[k] = fmaf(wgt, Cc.x, C2[k]);
-          T[k] = ok ? Tn : T[k];
-          cut[k] = ok ? cut[k] : INFINITY;
+          const float wgt = ok ? al * st.T : 0.0f;
+          st.C0 = fmaf(wgt, B[j].z, st.C0);
+          st.C1 = fmaf(wgt, B[j].w, st.C1);
+          st.C2 = fmaf(wgt, c2[j], st.C2);
+          st.T = ok ? Tn : st.T;
+          st.cut = ok ? st.cut : INFINITY;
           if (AUX) {
-            Ws[k] += wgt;
-            nblend[k] += ok ? 1u : 0u;
-            nstop[k] = ok ? nstop[k] : nseen[k];
-            nlast[k] = ok ? nseen[k] : nlast[k];
+            st.W += wgt;
+            st.nblend += ok ? 1u : 0u;
+            st.nstop = ok ? st.nstop : row_base + (uint32_t)ri[j] + 1u;
+            st.last = ok ? row_base + (uint32_t)ri[j] + 1u : st.last;
           }
         }
       }
     }
   }
+}
 
+// Stages Gaussian g as row `pos`: centre relative to (ox, oy); the quadrant test in the frame of
+// the tile at (tx0, ty0).
+template <typename SM>
+__device__ __forceinline__ void stage_row(SM &sm, int pos, double2 m, float4 co, float4 cl, int ox, int oy, int tx0,
+                                          int ty0, bool all_rows) {
+  sm.a[pos] = make_float4((float)(m.x - ox), (float)(m.y - oy), -0.5f * kLog2e * co.x, -kLog2e * co.y);
+  sm.b[pos] = make_float4(-0.5f * kLog2e * co.z, __log2f(co.w), cl.x, cl.y);
+  sm.c[pos] = cl.z;
+  const float ut = (float)(m.x - ((double)tx0 + 8.5)), vt = (float)(m.y - ((double)ty0 + 8.5));
+  sm.qm[pos] = all_rows ? (uint8_t)0xF
+                        : (uint8_t)mfma::quad_mask(ut, vt, co.x, co.y, co.z, mfma::log2_opacity(co.w));
+}
+
+template <bool AUX>
+__device__ __forceinline__ void write_pixel(const RasterJob &J, const RasterParams &P, int xx, int yy,
+                                            const PixelState &st, uint32_t rows_done) {
+  if (xx >= J.W || yy >= J.H) return;
   const int64_t HW = (int64_t)J.W * J.H;
-#pragma unroll
-  for (int k = 0; k < NT; ++k) {
-    const int xx = ox + (k % G) * kTile + px, yy = oy + (k / G) * kTile + py;
-    if (xx >= J.W || yy >= J.H) continue;
-    const int64_t pix = (int64_t)yy * J.W + xx;
-    J.image[pix] = C0[k] + T[k] * P.bg[0];
-    J.image[HW + pix] = C1[k] + T[k] * P.bg[1];
-    J.image[2 * HW + pix] = C2[k] + T[k] * P.bg[2];
-    if (AUX) {
-      int plane = 0;
-      if (P.aux_flags & GS_AUX_TFINAL) J.aux[(plane++) * HW + pix] = T[k];
-      if (P.aux_flags & GS_AUX_WSUM) J.aux[(plane++) * HW + pix] = Ws[k];
-      if (P.aux_flags & GS_AUX_NEVAL) {
-        const bool stopped = (cut[k] == INFINITY);
-        J.aux[(plane++) * HW + pix] = (float)(stopped ? nstop[k] : nseen[k]);
-      }
-      if (P.aux_flags & GS_AUX_NBLEND) J.aux[(plane++) * HW + pix] = (float)nblend[k];
-      if (P.aux_flags & GS_AUX_LAST) J.aux[(plane++) * HW + pix] = (float)nlast[k];
+  const int64_t pix = (int64_t)yy * J.W + xx;
+  J.image[pix] = st.C0 + st.T * P.bg[0];
+  J.image[HW + pix] = st.C1 + st.T * P.bg[1];
+  J.image[2 * HW + pix] = st.C2 + st.T * P.bg[2];
+  if (AUX) {
+    int plane = 0;
+    if (P.aux_flags & GS_AUX_TFINAL) J.aux[(plane++) * HW + pix] = st.T;
+    if (P.aux_flags & GS_AUX_WSUM) J.aux[(plane++) * HW + pix] = st.W;
+    if (P.aux_flags & GS_AUX_NEVAL) {
+      const bool stopped = (st.cut == INFINITY);
+      J.aux[(plane++) * HW + pix] = (float)(stopped ? st.nstop : rows_done);
     }
+    if (P.aux_flags & GS_AUX_NBLEND) J.aux[(plane++) * HW + pix] = (float)st.nblend;
+    if (P.aux_flags & GS_AUX_LAST) J.aux[(plane++) * HW + pix] = (float)st.last;
   }
 }
 
-// One workgroup per bin, in the XCD-aware order of the MFMA rasterizer.
+// Renders work item `item` of job J (one workgroup): a tile (G == 1) or member tile
+// item % G^2 (row-major) of group item / G^2.  Shared by the single-image and batched kernels.
+template <int G, bool AUX, typename SM>
+__device__ __forceinline__ void raster_item_fp32(const RasterJob &J, const RasterParams &P, int item, SM &sm) {
+  constexpr int NT = G * G, CAP = SM::CAP;
+  const int bin = item / NT, k = item % NT;
+  const int ox = (bin % J.GX) * G * kTile, oy = (bin / J.GX) * G * kTile;
+  const int tx0 = ox + (k % G) * kTile, ty0 = oy + (k / G) * kTile;
+  if (G > 1 && (tx0 >= J.W || ty0 >= J.H)) return;   // a member tile past the image (uniform)
+  const uint32_t start = J.ranges[2 * bin], end = J.ranges[2 * bin + 1];
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const int px = (w & 1) * 8 + (lane & 7), py = (w >> 1) * 8 + (lane >> 3);
+  const float X = (float)(tx0 - ox + px) + 0.5f, Y = (float)(ty0 - oy + py) + 0.5f;
+  PixelState st;
+  st.T = 1.0f; st.C0 = st.C1 = st.C2 = 0.0f; st.W = 0.0f;
+  st.cut = (tx0 + px < J.W) && (ty0 + py < J.H) ? kCutLog2 : INFINITY;
+  st.nstop = 0; st.nblend = 0; st.last = 0;
+  uint32_t rows_done = 0;   // uniform: entries of the tile's list blended so far
+  if (t == 0) {             // the row of the list slots past a wave's last row
+    sm.a[CAP] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    sm.b[CAP] = make_float4(0.0f, -INFINITY, 0.0f, 0.0f);
+    sm.c[CAP] = 0.0f;
+  }
+  int it = 0;
+
+  if constexpr (G == 1) {
+    for (uint32_t cs = start; cs < end; cs += kBlock) {
+      const int cnt = (int)min((uint32_t)kBlock, end - cs);
+      if (it > 0) {
+        // every wave is done with the previous chunk and has posted whether it still blends
+        __syncthreads();
+        const uint32_t *al = sm.alive[(it - 1) & 1];
+        if (!(al[0] | al[1] | al[2] | al[3])) break;
+      }
+      if (t < cnt) {
+        const uint32_t g = J.vals[cs + t];
+        stage_row(sm, t, J.xy[g], J.conic[g], J.rgb[g], ox, oy, tx0, ty0, P.all_rows);
+      }
+      __syncthreads();
+      const int nw = mfma::wave_list(sm.qm, cnt, sm.wl[w]);
+      blend_rows<AUX>(sm, sm.wl[w], nw, X, Y, st, rows_done);
+      rows_done += (uint32_t)cnt;
+      const uint64_t bal = __ballot(st.cut != INFINITY);
+      if (lane == 0) sm.alive[it & 1][w] = bal != 0;
+      ++it;
+    }
+  } else {
+    int filled = 0;   // uniform: rows in the buffer
+    auto blend = [&]() {
+      const int nw = mfma::wave_list(sm.qm, filled, sm.wl[w]);
+      blend_rows<AUX>(sm, sm.wl[w], nw, X, Y, st, rows_done);
+      rows_done += (uint32_t)filled;
+      filled = 0;
+    };
+    bool live = true;
+    for (uint32_t cs = start; cs < end; cs += kBlock) {
+      if (filled > CAP - kBlock) {   // another step might not fit
+        __syncthreads();
+        blend();
+        const uint64_t ab = __ballot(st.cut != INFINITY);
+        if (lane == 0) sm.alive[0][w] = ab != 0;
+        __syncthreads();
+        if (!(sm.alive[0][0] | sm.alive[0][1] | sm.alive[0][2] | sm.alive[0][3])) {
+          live = false;
+          break;
+        }
+      }
+      const int cnt = (int)min((uint32_t)kBlock, end - cs);
+      bool mine = false;
+      double2 m = make_double2(0.0, 0.0);
+      float4 co = make_float4(0.0f, 0.0f, 0.0f, 0.0f), cl = co;
+      if (t < cnt) {
+        mine = (static_cast<const uint16_t *>(J.masks)[cs + t] >> k) & 1u;
+        if (mine) {
+          const uint32_t g = J.vals[cs + t];
+          m = J.xy[g];
+          co = J.conic[g];
+          cl = J.rgb[g];
+        }
+      }
+      const uint64_t bk = __ballot(mine);
+      if (lane == 0) sm.wcnt[it & 1][w] = (uint32_t)__popcll(bk);
+      __syncthreads();
+      const uint4 ck = *reinterpret_cast<const uint4 *>(sm.wcnt[it & 1]);
+      if (mine) {
+        const uint32_t woff = (w > 0 ? ck.x : 0u) + (w > 1 ? ck.y : 0u) + (w > 2 ? ck.z : 0u);
+        const int pos = filled + (int)(woff + __builtin_amdgcn_mbcnt_hi((uint32_t)(bk >> 32),
+                                                                        __builtin_amdgcn_mbcnt_lo((uint32_t)bk, 0u)));
+        stage_row(sm, pos, m, co, cl, ox, oy, tx0, ty0, P.all_rows);
+      }
+      filled += (int)(ck.x + ck.y + ck.z + ck.w);
+      ++it;
+    }
+    if (live && filled > 0) {
+      __syncthreads();
+      blend();
+    }
+  }
+  write_pixel<AUX>(J, P, tx0 + px, ty0 + py, st, rows_done);
+}
+
+// rows of LDS: one chunk for a tile, a buffer that takes a step of 256 on top of up to 192 for a
+// member tile (as in gs_raster_mfma.hip)
+template <int G>
+using SharedOf = Fp32Shared<G == 1 ? kBlock : 448>;
+
+// One workgroup per tile, in the XCD-aware order of the MFMA rasterizer, or per member tile.
 template <int G, bool AUX>
 __global__ __launch_bounds__(kBlock) void k_raster_fp32(RasterJob J, RasterParams P) {
-  __shared__ Fp32Shared sm;
-  const int item = xcd_raster_bin((int)blockIdx.x, J.GX, J.GY);
+  __shared__ SharedOf<G> sm;
+  const int item = G == 1 ? xcd_raster_bin((int)blockIdx.x, J.GX, J.GY) : (int)blockIdx.x;
   if (item < 0) return;
-  raster_bin_fp32<G, AUX>(J, P, item, sm);
+  raster_item_fp32<G, AUX>(J, P, item, sm);
 }
 
 // Persistent batched rasterizer (see the MFMA variant).
 template <int G, bool AUX>
 __global__ __launch_bounds__(kBlock) void k_raster_fp32_batch(const BatchTable tb,
                                                               RasterParams P, uint32_t *counter) {
-  __shared__ Fp32Shared sm;
+  __shared__ SharedOf<G> sm;
   __shared__ int s_item;
   batch_items(counter, tb.total, &s_item, [&](int item) {
     int lo = 0, hi = tb.n_jobs;   // last job with bin0 <= item
@@ -151,7 +257,7 @@ __global__ __launch_bounds__(kBlock) void k_raster_fp32_batch(const BatchTable t
       if (tb.jobs[mid].bin0 <= item) lo = mid; else hi = mid;
     }
     const RasterJob J = tb.jobs[lo];
-    raster_bin_fp32<G, AUX>(J, P, item - J.bin0, sm);
+    raster_item_fp32<G, AUX>(J, P, item - J.bin0, sm);
   });
 }
 
@@ -167,7 +273,8 @@ hipError_t launch_g(const RasterJob &j, const RasterParams &p, const BatchArgs *
     hipLaunchKernelGGL((k_raster_fp32_batch<G, AUX>), dim3((unsigned)b->grid), dim3(kBlock), 0, st, *b->table, p,
                        b->counter);
   } else {
-    hipLaunchKernelGGL((k_raster_fp32<G, AUX>), dim3(xcd_raster_grid(j.GX, j.GY)), dim3(kBlock), 0, st, j, p);
+    const unsigned grid = G == 1 ? xcd_raster_grid(j.GX, j.GY) : (unsigned)j.items;
+    hipLaunchKernelGGL((k_raster_fp32<G, AUX>), dim3(grid), dim3(kBlock), 0, st, j, p);
   }
   return hipGetLastError();
 }
