@@ -110,7 +110,7 @@ __global__ __launch_bounds__(kBlock) void k_raster_backward(BackwardJob J) {
   if (t == 0) sm.last = start;
   for (uint32_t cs = start; cs < end; cs += kBlock) {
     const int cnt = (int)min((uint32_t)kBlock, end - cs);
-    __syncthreads();
+    block_sync();
     stage(J, sm, cs, cnt, ox, oy);
     if (!__syncthreads_or(cut != INFINITY)) break;
     for (int j = 0; j < cnt; ++j) {
@@ -130,9 +130,9 @@ __global__ __launch_bounds__(kBlock) void k_raster_backward(BackwardJob J) {
       }
     }
   }
-  __syncthreads();
+  block_sync();
   atomicMax(&sm.last, last);
-  __syncthreads();
+  block_sync();
   const uint32_t tile_last = sm.last;
 
   // pass 2: back to front
@@ -146,9 +146,9 @@ __global__ __launch_bounds__(kBlock) void k_raster_backward(BackwardJob J) {
   for (uint32_t ce = tile_last; ce > start;) {
     const int cnt = (int)min((uint32_t)kBlock, ce - start);
     const uint32_t cs = ce - (uint32_t)cnt;
-    __syncthreads();
+    block_sync();
     stage(J, sm, cs, cnt, ox, oy);
-    __syncthreads();
+    block_sync();
     for (int j = cnt - 1; j >= 0; --j) {
       const float4 A = sm.a[j];
       const float4 B = sm.b[j];
@@ -236,9 +236,9 @@ __global__ __launch_bounds__(kBlock) void k_raster_backward_mfma(BackwardJob J, 
   // entry outside the tile is read)
   const uint32_t last = inside ? min((uint32_t)J.last[pix], len) : 0u;
   if (t == 0) sm.last = 0;
-  __syncthreads();
+  block_sync();
   atomicMax(&sm.last, last);
-  __syncthreads();
+  block_sync();
   const uint32_t tile_last = sm.last;
 
   const float gp0 = inside ? J.dimage[pix] : 0.0f;
@@ -252,7 +252,7 @@ __global__ __launch_bounds__(kBlock) void k_raster_backward_mfma(BackwardJob J, 
   for (uint32_t ce = tile_last; ce > 0;) {
     const int cnt = (int)min((uint32_t)kBlock, ce);
     const uint32_t cs = ce - (uint32_t)cnt;   // positions in the tile's list
-    __syncthreads();
+    block_sync();
     if (t < cnt) {
       const uint32_t g = J.vals[start + cs + t];
       const double2 m = J.xy[g];
@@ -266,7 +266,7 @@ __global__ __launch_bounds__(kBlock) void k_raster_backward_mfma(BackwardJob J, 
       sm.p2[t] = make_float2(cl.z, __uint_as_float(g));
       sm.qm[t] = all_rows ? (uint8_t)0xF : (uint8_t)mfma::quad_mask(u, v, co.x, co.y, co.z, l2o);
     }
-    __syncthreads();
+    block_sync();
     const int n = mfma::wave_list(sm.qm, cnt, sm.wl[w]);
     for (int blk = ((n + 31) >> 5) - 1; blk >= 0; --blk) {
       const int slot = 32 * blk + (lane & 31);

@@ -17,6 +17,16 @@ constexpr float kLn2 = 0.6931471805599453f;
 // log2(1/255): the 1/255 alpha cut taken on log2(alpha)
 constexpr float kCutLog2 = -7.994353436858858f;
 
+// Workgroup barrier.  The wave's LDS operations are waited for explicitly: at a barrier in a loop
+// header the compiler leaves that wait out for LDS writes pending over the back edge (seen in the
+// code it made for the raster loops' "still blending" flags), and a wave that reads such a
+// flag after the barrier may then see the old value and leave the loop at another step than
+// the rest.
+__device__ __forceinline__ void block_sync() {
+  __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0), the other counters unconstrained
+  __syncthreads();
+}
+
 struct Grid {
   int W, H, TX, TY, G, GX, GY;
   int64_t nbins;
@@ -368,9 +378,9 @@ __device__ __forceinline__ void batch_items(uint32_t *counters, int total, int *
     const int64_t i = batch_item(atomicAdd(ctr, 1u), seq);
     *s_item = i < total ? (int)i : total;
   }
-  __syncthreads();
+  block_sync();
   int it = *s_item;
-  __syncthreads();
+  block_sync();
   while (it < total) {
     uint32_t nxt = 0;
     if (threadIdx.x == 0) nxt = atomicAdd(ctr, 1u);
@@ -379,9 +389,9 @@ __device__ __forceinline__ void batch_items(uint32_t *counters, int total, int *
       const int64_t i = batch_item(nxt, seq);
       *s_item = i < total ? (int)i : total;
     }
-    __syncthreads();
+    block_sync();
     it = *s_item;
-    __syncthreads();
+    block_sync();
   }
 }
 

@@ -55,7 +55,7 @@ __device__ __forceinline__ T block_exclusive_scan(T v, T *sh4, T *total) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const T incl = wave_inclusive_scan<T>(v);
   if (lane == 63) sh4[w] = incl;
-  __syncthreads();
+  block_sync();
   T before = 0, all = 0;
 #pragma unroll
   for (int k = 0; k < kBlock / 64; ++k) {
@@ -63,7 +63,7 @@ __device__ __forceinline__ T block_exclusive_scan(T v, T *sh4, T *total) {
     before += k < w ? x : (T)0;
     all += x;
   }
-  __syncthreads();
+  block_sync();
   *total = all;
   return before + incl - v;
 }

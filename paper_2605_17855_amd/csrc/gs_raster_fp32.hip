@@ -159,7 +159,7 @@ __device__ __forceinline__ void raster_item_fp32(const RasterJob &J, const Raste
       const int cnt = (int)min((uint32_t)kBlock, end - cs);
       if (it > 0) {
         // every wave is done with the previous chunk and has posted whether it still blends
-        __syncthreads();
+        block_sync();
         const uint32_t *al = sm.alive[(it - 1) & 1];
         if (!(al[0] | al[1] | al[2] | al[3])) break;
       }
@@ -167,7 +167,7 @@ __device__ __forceinline__ void raster_item_fp32(const RasterJob &J, const Raste
         const uint32_t g = J.vals[cs + t];
         stage_row(sm, t, J.xy[g], J.conic[g], J.rgb[g], ox, oy, tx0, ty0, P.all_rows);
       }
-      __syncthreads();
+      block_sync();
       const int nw = mfma::wave_list(sm.qm, cnt, sm.wl[w]);
       blend_rows<AUX>(sm, sm.wl[w], nw, X, Y, st, rows_done);
       rows_done += (uint32_t)cnt;
@@ -186,11 +186,11 @@ __device__ __forceinline__ void raster_item_fp32(const RasterJob &J, const Raste
     bool live = true;
     for (uint32_t cs = start; cs < end; cs += kBlock) {
       if (filled > CAP - kBlock) {   // another step might not fit
-        __syncthreads();
+        block_sync();
         blend();
         const uint64_t ab = __ballot(st.cut != INFINITY);
         if (lane == 0) sm.alive[0][w] = ab != 0;
-        __syncthreads();
+        block_sync();
         if (!(sm.alive[0][0] | sm.alive[0][1] | sm.alive[0][2] | sm.alive[0][3])) {
           live = false;
           break;
@@ -211,7 +211,7 @@ __device__ __forceinline__ void raster_item_fp32(const RasterJob &J, const Raste
       }
       const uint64_t bk = __ballot(mine);
       if (lane == 0) sm.wcnt[it & 1][w] = (uint32_t)__popcll(bk);
-      __syncthreads();
+      block_sync();
       const uint4 ck = *reinterpret_cast<const uint4 *>(sm.wcnt[it & 1]);
       if (mine) {
         const uint32_t woff = (w > 0 ? ck.x : 0u) + (w > 1 ? ck.y : 0u) + (w > 2 ? ck.z : 0u);
@@ -223,7 +223,7 @@ __device__ __forceinline__ void raster_item_fp32(const RasterJob &J, const Raste
       ++it;
     }
     if (live && filled > 0) {
-      __syncthreads();
+      block_sync();
       blend();
     }
   }

@@ -247,7 +247,7 @@ __device__ __forceinline__ void raster_bin_mfma_group(const RasterJob &J, const 
     const int cnt = (int)min((uint32_t)CH, end - cs);
     if (it > 0) {
       // every wave is done with the previous chunk and has posted whether it still blends
-      __syncthreads();
+      block_sync();
       uint32_t any = 0;
 #pragma unroll
       for (int v = 0; v < NW; ++v) any |= sm.alive[(it - 1) & 1][v];
@@ -287,7 +287,7 @@ __device__ __forceinline__ void raster_bin_mfma_group(const RasterJob &J, const 
         if (lane == 0) sm.wcnt[jj][w] = (uint32_t)__popcll(bk);
       }
     }
-    __syncthreads();
+    block_sync();
     if (AUX) {
       // each row's position in every member tile's list (entries of the chunk with its bit)
 #pragma unroll
@@ -298,7 +298,7 @@ __device__ __forceinline__ void raster_bin_mfma_group(const RasterJob &J, const 
         sm.tpos[jj][t] = (uint16_t)(woff + __builtin_amdgcn_mbcnt_hi((uint32_t)(bk >> 32),
                                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)bk, 0u)));
       }
-      __syncthreads();
+      block_sync();
     }
     // one copy of the tile step: the member tile's state is moved into registers for it
 #pragma unroll 1
@@ -395,7 +395,7 @@ __device__ __forceinline__ void raster_bin_mfma(const RasterJob &J, const Raster
     if (it > 0) {
       // every wave is done with the previous chunk (single buffer) and has posted whether its
       // pixels are still blending
-      __syncthreads();
+      block_sync();
       const uint32_t any = sm.alive[(it - 1) & 1][0] | sm.alive[(it - 1) & 1][1] | sm.alive[(it - 1) & 1][2] |
                            sm.alive[(it - 1) & 1][3];
       if (!any) break;
@@ -414,7 +414,7 @@ __device__ __forceinline__ void raster_bin_mfma(const RasterJob &J, const Raster
       sm.col[2][t] = cl.z;
       sm.qm[t] = P.all_rows ? (uint8_t)0xF : (uint8_t)quad_mask(u, v, co.x, co.y, co.z, l2o);
     }
-    __syncthreads();
+    block_sync();
     const int nw = wave_list(sm.qm, cnt, sm.wl[w]);
     process_rows<PREC, S, AUX>(sm.A, &sm.col[0][0], sm.wl[w], nw, sm.wc[w], B0, B1, B20, B21, st, rows_done);
     rows_done += cnt;
@@ -465,11 +465,11 @@ __device__ __forceinline__ void raster_member_tile(const RasterJob &J, const Ras
     if (filled > CAP - kBlock) {
       // the rows of the earlier steps are in place; then every wave is done reading them and
       // has posted whether its pixels are still blending
-      __syncthreads();
+      block_sync();
       blend();
       const uint64_t ab = __ballot(st.cut != INFINITY);
       if (lane == 0) sm.alive[w] = ab != 0;
-      __syncthreads();
+      block_sync();
       if (!(sm.alive[0] | sm.alive[1] | sm.alive[2] | sm.alive[3])) {
         live = false;
         break;
@@ -493,7 +493,7 @@ __device__ __forceinline__ void raster_member_tile(const RasterJob &J, const Ras
     }
     const uint64_t bk = __ballot(mine);
     if (lane == 0) sm.wcnt[cp][w] = (uint32_t)__popcll(bk);
-    __syncthreads();
+    block_sync();
     const uint4 ck = *reinterpret_cast<const uint4 *>(sm.wcnt[cp]);
     if (mine) {
       const uint32_t woff = (w > 0 ? ck.x : 0u) + (w > 1 ? ck.y : 0u) + (w > 2 ? ck.z : 0u);
@@ -511,7 +511,7 @@ __device__ __forceinline__ void raster_member_tile(const RasterJob &J, const Ras
     cp ^= 1;
   }
   if (live && filled > 0) {
-    __syncthreads();
+    block_sync();
     blend();
   }
   write_tile<AUX>(J, P, tx0 + px, ty0 + py, st, rows_done);

@@ -81,7 +81,7 @@ __device__ __forceinline__ T block_exclusive_scan_t(T v, T *sh4, T *total) {
     if (lane >= off) incl += u;
   }
   if (lane == 63) sh4[w] = incl;
-  __syncthreads();
+  block_sync();
   T before = 0, all = 0;
 #pragma unroll
   for (int k = 0; k < kBlock / 64; ++k) {
@@ -89,7 +89,7 @@ __device__ __forceinline__ T block_exclusive_scan_t(T v, T *sh4, T *total) {
     before += k < w ? x : (T)0;
     all += x;
   }
-  __syncthreads();
+  block_sync();
   *total = all;
   return before + incl - v;
 }
@@ -147,7 +147,7 @@ __global__ __launch_bounds__(kBlock) void k_radix_count(const KT *keys, uint64_t
 #pragma unroll
     for (int r = 0; r < kRounds; ++r) c[r] = base + (uint64_t)r * 64 + lane < n ? wt.count[c[r]] : 0u;
   }
-  __syncthreads();
+  block_sync();
 #pragma unroll
   for (int r = 0; r < kRounds; ++r) {
     const bool valid = base + (uint64_t)r * 64 + lane < n;
@@ -157,7 +157,7 @@ __global__ __launch_bounds__(kBlock) void k_radix_count(const KT *keys, uint64_t
       if (WEIGHTED) atomicAdd(&hw[d], c[r]);
     }
   }
-  __syncthreads();
+  block_sync();
   for (int d = t; d < ndig; d += kBlock) {
     counts[(uint64_t)d * tiles_max + tile] = h[d];
     if (WEIGHTED) wt.wcounts[(uint64_t)d * tiles_max + tile] = hw[d];
@@ -293,7 +293,7 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const KT *kin, const u
 #pragma unroll
   for (int k = 0; k < 4; ++k)
     for (int d = t; d < ndig; d += kBlock) wcnt[k][d] = 0;
-  __syncthreads();
+  block_sync();
 #pragma unroll
   for (int r = 0; r < kRounds; ++r) {
     const bool valid = base + (uint64_t)r * 64 + lane < n;
@@ -315,7 +315,7 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const KT *kin, const u
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
-  __syncthreads();
+  block_sync();
   // per digit: tile-local start (scan over digits of the tile's counts) and global start
   // (scan over digits of the totals, plus this tile's offset within the digit)
   uint32_t c[M][4], loc = 0, gsum = 0;
@@ -351,7 +351,7 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const KT *kin, const u
     if (WEIGHTED) wb += wtot_d[j];
   }
   if (WEIGHTED && tile == 0 && t == 0) fe.dpos[n] = wall;
-  __syncthreads();
+  block_sync();
 #pragma unroll
   for (int r = 0; r < kRounds; ++r) {
     const uint64_t i = base + (uint64_t)r * 64 + lane;
@@ -362,7 +362,7 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const KT *kin, const u
       if (WEIGHTED) s_w[lp] = kw[r];
     }
   }
-  __syncthreads();
+  block_sync();
   const uint32_t nvalid = (uint32_t)((n - tile0) < (uint64_t)kSortTile ? (n - tile0) : (uint64_t)kSortTile);
   if (WEIGHTED) {
     // exclusive scan of the weights in tile-local sorted order (R consecutive keys per thread;
@@ -381,7 +381,7 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const KT *kin, const u
       s_wx[t * kRounds + q] = ex;
       ex += x[q];
     }
-    __syncthreads();
+    block_sync();
     for (uint32_t i = t; i < nvalid; i += kBlock) {
       const KT k = s_key[i];
       const uint32_t d = (uint32_t)(k >> shift) & dmask;
@@ -455,7 +455,7 @@ __global__ __launch_bounds__(kBlock) void k_depth_keys(const uint32_t *order, co
   const uint64_t tile0 = (uint64_t)tile * kSortTile;
   const int ndig = 1 << nbits0;
   for (int d = threadIdx.x; d < ndig; d += kBlock) h[d] = 0;
-  __syncthreads();
+  block_sync();
   const uint32_t dmask = (1u << nbits0) - 1u;
   uint32_t g[R];
 #pragma unroll
@@ -472,7 +472,7 @@ __global__ __launch_bounds__(kBlock) void k_depth_keys(const uint32_t *order, co
       atomicAdd(&h[k & dmask], 1u);
     }
   }
-  __syncthreads();
+  block_sync();
   for (int d = threadIdx.x; d < ndig; d += kBlock) dcounts[(uint64_t)d * tiles + tile] = h[d];
 }
 
@@ -551,14 +551,14 @@ __device__ __forceinline__ void stage_block_gaussians(const uint64_t *dpos, cons
     }
     if (lane == 0) *s_first = lo;
   }
-  __syncthreads();
+  block_sync();
   *first = *s_first;
   *span = (nvis - *first) < (uint32_t)ITEMS ? (nvis - *first) : (uint32_t)ITEMS;
   for (uint32_t i = t; i <= *span; i += kBlock) {
     s_pos[i] = dpos[*first + i];
     if (s_g && i < *span) s_g[i] = order[*first + i];
   }
-  __syncthreads();
+  block_sync();
 }
 
 // The first radix pass's per-tile digit counts, taken where the keys are written (the binning
@@ -621,7 +621,7 @@ __global__ __launch_bounds__(kBlock) void k_binning(const uint32_t *order, const
     }
   }
   if (fc.counts) {
-    __syncthreads();
+    block_sync();
     for (int d = threadIdx.x; d < (1 << fc.nbits0); d += kBlock) fc.counts[(uint64_t)d * fc.tiles + tile] = h[d];
   }
 }
@@ -750,7 +750,7 @@ __global__ __launch_bounds__(kBlock) void k_binning_tight(const uint32_t *order,
     }
   }
   if (fc.counts) {
-    __syncthreads();
+    block_sync();
     for (int d = threadIdx.x; d < (1 << fc.nbits0); d += kBlock) fc.counts[(uint64_t)d * fc.tiles + tile] = h[d];
   }
 }
