@@ -45,7 +45,8 @@ typedef struct {
  * four buffers must be ordinary (coarse-grained) device memory, as hipMalloc returns.
  * proj and bins are what gs_preprocess and gs_bin_sort wrote (opacity-aware bins, from
  * GS_OPT_TIGHT, give the same gradients).  Reads opt->group, which must be 1 (tile bins;
- * GS_ERR_UNSUPPORTED otherwise), and opt->bg; ignores the precision and the aux flags.
+ * GS_ERR_UNSUPPORTED otherwise), opt->bg and GS_OPT_ALL_ROWS (every row in every quadrant: the
+ * same gradients up to the order of the sums); ignores the precision and the aux flags.
  * Asynchronous on `stream`. */
 gs_status gs_rasterize_backward(const gs_projected *proj, const gs_bins *bins, const gs_camera *cam,
                                 const gs_options *opt, const float *dimage, const gs_grads *grads,

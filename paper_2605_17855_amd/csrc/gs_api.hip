@@ -487,7 +487,7 @@ gs_status gs_rasterize_backward(const gs_projected *proj, const gs_bins *bins, c
   gsi::BackwardJob j;
   const gs_status s = backward_job(proj, bins, cam, opt, dimage, grads, &j);
   if (s) return s;
-  GS_HIP(gsi::launch_raster_backward(j, static_cast<hipStream_t>(stream)));
+  GS_HIP(gsi::launch_raster_backward(j, (opt->flags & GS_OPT_ALL_ROWS) != 0, static_cast<hipStream_t>(stream)));
   return GS_OK;
 }
 

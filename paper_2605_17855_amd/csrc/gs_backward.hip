@@ -1,277 +1,512 @@
-// Backward pass of the FP32 compositing: the derivative of the forward recurrence of the
-// plain rasterizer (paper, Background: eq. power_d, eq. power, the 1/255 cut, the 0.99
-// clamp, the 1e-4 stop) on the branch the forward takes.
+// Backward pass of the compositing: the derivative of the forward recurrence (paper,
+// Background: eq. power_d, eq. power, the 1/255 cut, the 0.99 clamp, the 1e-4 stop) on the
+// branch the forward takes.
 //
-// One 256-lane workgroup per 16x16 tile, one pixel per lane, 8x8 quadrants per wave as in
-// the forward.  Two passes over the tile's depth-sorted list, each staged through LDS in
-// chunks of 256 entries:
-//  1. the forward recurrence again, in the forward rasterizer's FP32 arithmetic (the same
-//     operations in the same order, so every cut, clamp and stop is decided the same way),
-//     for the pixel's final transmittance T_end and the end of its blended prefix;
-//  2. the list back to front.  T_i = T_{i+1} / (1 - alpha_i) (a 1-ulp hardware reciprocal)
-//     recovers the transmittance in front of each blended Gaussian and S, the colour the
-//     later Gaussians add, grows by c_i alpha_i T_i.  A pair's nine gradient terms are
-//     summed over the wave (a reduce-scatter with lane swaps, then DPP row sums) and nine
-//     lanes add them to the Gaussian's gradients, one hardware FP32 atomic add each (the
-//     buffers are ordinary device memory).
+// One 256-lane workgroup per 16x16 tile, one pixel per lane, 8x8 quadrants per wave as in the
+// forward; each wave walks only the rows whose alpha can reach the cut in its quadrant (the
+// forward's masks).  The tile's list is taken back to front in chunks of 256 entries.  Per
+// (row, pixel) pair, T_i = T_{i+1} / (1 - alpha_i) (a 1-ulp hardware reciprocal) recovers the
+// transmittance in front of a blended Gaussian, and s, the upstream gradient's product with the
+// colour that the later Gaussians and the background add, grows by alpha_i T_i (g . c_i):
+//   dL/dalpha_i = T_i (g . c_i) - s / (1 - alpha_i),   p_i = dL/dpower_i = alpha_i dL/dalpha_i.
+//
+// Sums over pixels.  A row's nine gradients are linear in nine sums over the wave's pixels: the
+// six moments sum p (1, x, y, x^2, xy, y^2) in the tile's frame and sum alpha T g (three
+// channels).  For 8 rows at a time they are one FP32 matrix product, (8 rows of p over 8 rows of
+// alpha T) x 64 pixels by 64 pixels x (6 monomials, 3 channels of g): v_mfma_f32_16x16x4_f32,
+// FP32 in, FP32 accumulate.  Its pixel side stays in 16 registers; the row side is transposed
+// through a wave-private LDS buffer.  (p by g and alpha T by the monomials are computed too and
+// not used: the two separate 16-row products that leave them out take as many matrix
+// instructions and 21 more registers.)  The four waves of a tile add their sums in LDS
+// and one thread per entry turns the moments into gradients and adds them with hardware FP32
+// atomics, once per (entry, tile).  Wave sums by lane swaps and DPP took ~45 vector instructions
+// per row and one nine-lane global atomic per (row, quadrant).
 #include "gs_backward.hpp"
 #include "gs_mfma.hpp"
 
 namespace gsi {
 namespace {
 
-struct BwdShared {
-  float4 a[kBlock];   // (u, v, -a/2 log2e, -b log2e): centre relative to the tile, power rows
-  float4 b[kBlock];   // (-c/2 log2e, log2 o, r, g)
-  float4 c[kBlock];   // (b colour, conic a, conic b, conic c)
-  float2 d[kBlock];   // (1 / opacity, Gaussian index bits)
-  uint32_t last;      // end of the longest blended prefix of the tile's pixels
+typedef float float4v __attribute__((ext_vector_type(4)));
+
+constexpr int kRowBlock = 8;         // rows per matrix product
+constexpr int kVStride = 68;         // floats per line of the transposing buffer: conflict-free 16-byte reads
+constexpr int kTerms = 9;
+
+// LDS of both kernels' sums.  acc: per staged entry, the six moments of p and the three colour
+// sums; after the conversion, its nine gradients.
+struct SumShared {
+  __align__(16) float v[4][2 * kRowBlock * kVStride];   // wave-private: lines of p, then of alpha T
+  float acc[kBlock * kTerms];
+  uint32_t g[kBlock];                               // the entries' Gaussians
+  __align__(4) uint8_t wl[4][kBlock];               // each wave's row list
+  uint8_t qm[kBlock];
+  uint32_t last;                                    // end of the longest blended prefix of the tile
 };
 
-template <int CTRL>
-__device__ __forceinline__ float dpp(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
+// A value the compiler takes as new: what is computed from it stays where it is used, instead of
+// being kept in registers across the row loops (the flush's indices alone took ~25).
+__device__ __forceinline__ int fresh(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
 }
 
-// Sum over the 16 lanes of each row (every lane of the row gets it): quad_perm [1,0,3,2] and
-// [2,3,0,1], then the half-row and row mirrors.
-__device__ __forceinline__ float row_sum(float v) {
-  v += dpp<0xB1>(v);
-  v += dpp<0x4E>(v);
-  v += dpp<0x141>(v);
-  v += dpp<0x140>(v);
-  return v;
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Reduce-scatter steps of two registers at once.  swap32_add: lanes 0..31 get a[i] + a[i+32],
-// lanes 32..63 get b[i-32] + b[i].  swap16_add (rows of 16 lanes): row 0 gets a's rows 0 + 1,
-// row 1 b's rows 0 + 1, row 2 a's rows 2 + 3, row 3 b's rows 2 + 3.
-__device__ __forceinline__ float swap32_add(float a, float b) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-__device__ __forceinline__ float swap16_add(float a, float b) {
-  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
+// This lane's share of the pixel-side operand: column n = lane % 16, pixels 16 (lane / 16) + j of
+// the wave's quadrant for j < 16.  Columns 0..5 are the monomials of the pixel (centred on the
+// tile, so |x|, |y| <= 7.5), 6..8 the channels of its upstream gradient, the others zero.  A
+// pixel whose upstream gradient is not finite has zeros there and adds its terms by itself, so
+// that it reaches only the Gaussians it blends.
+struct PixelSide {
+  float b[16];
+};
 
-// Wave sums of the nine gradient terms v[0..8], added to the Gaussian's gradients by nine lanes
-// in one hardware FP32 atomic.  After the two swap steps the rows of x0 hold the partial sums
-// of terms (0, 2, 1, 3), those of x1 terms (4, 6, 5, 7) and every row of x2 term 8; a row sum
-// completes each.  Term f goes to rgb[3g + f] (f < 3), opacity[g] (3), conic[3g + f - 4]
-// (4..6), xy[2g + f - 7] (7, 8).
-__device__ __forceinline__ void add_terms(const BackwardJob &J, const float (&v)[9], uint32_t g, int lane) {
-  const float x0 = row_sum(swap16_add(swap32_add(v[0], v[1]), swap32_add(v[2], v[3])));
-  const float x1 = row_sum(swap16_add(swap32_add(v[4], v[5]), swap32_add(v[6], v[7])));
-  const float w8 = swap32_add(v[8], v[8]);
-  const float x2 = row_sum(swap16_add(w8, w8));
-  const int row = lane >> 4, c = lane & 15;
-  if (c < 2 || (c == 2 && row == 0)) {
-    const int rf = row == 1 ? 2 : row == 2 ? 1 : row;
-    const int f = c == 0 ? rf : c == 1 ? 4 + rf : 8;
-    const float val = c == 0 ? x0 : c == 1 ? x1 : x2;
-    const size_t G = g;
-    float *dst = f < 3 ? J.g_rgb + 3 * G + f
-               : f == 3 ? J.g_op + G
-               : f < 7 ? J.g_conic + 3 * G + (f - 4)
-               : J.g_xy + 2 * G + (f - 7);
-    unsafeAtomicAdd(dst, val);
+__device__ __forceinline__ PixelSide pixel_side(const BackwardJob &J, int ox, int oy) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int n = lane & 15;
+  const int64_t HW = (int64_t)J.W * J.H;
+  PixelSide s;
+#pragma unroll
+  for (int j = 0; j < 16; ++j) {
+    const int p = 16 * (lane >> 4) + j;
+    const int px = (w & 1) * 8 + (p & 7), py = (w >> 1) * 8 + (p >> 3);
+    const float x = (float)px - 7.5f, y = (float)py - 7.5f;
+    s.b[j] = n == 0 ? 1.0f : n == 1 ? x : n == 2 ? y : n == 3 ? x * x : n == 4 ? x * y : n == 5 ? y * y : 0.0f;
+    if (n >= 6 && n < 9 && ox + px < J.W && oy + py < J.H) {
+      const int64_t pix = (int64_t)(oy + py) * J.W + (ox + px);
+      const float g0 = J.dimage[pix], g1 = J.dimage[HW + pix], g2 = J.dimage[2 * HW + pix];
+      const bool fin = fabsf(g0) < INFINITY && fabsf(g1) < INFINITY && fabsf(g2) < INFINITY;
+      s.b[j] = !fin ? 0.0f : n == 6 ? g0 : n == 7 ? g1 : g2;
+    }
   }
+  return s;
 }
 
-__device__ __forceinline__ void stage(const BackwardJob &J, BwdShared &sm, uint32_t cs, int cnt, int ox, int oy) {
-  const int t = threadIdx.x;
+// One entry's nine sums to its gradients: rgb (3), opacity, conic (3), xy (2), in place.
+// (u, v): the centre in the tile-centred frame.
+__device__ __forceinline__ void convert_sums(float *a, float u, float v, const float4 co) {
+  const float m0 = a[0], mx = a[1], my = a[2], mxx = a[3], mxy = a[4], myy = a[5];
+  const float r0 = a[6], r1 = a[7], r2 = a[8];
+  // an entry that no pixel blended (its record may be anything) adds nothing
+  if (m0 == 0.0f && mx == 0.0f && my == 0.0f && mxx == 0.0f && mxy == 0.0f && myy == 0.0f) {
+    a[0] = r0;
+    a[1] = r1;
+    a[2] = r2;
+    a[6] = a[7] = a[8] = 0.0f;
+    return;
+  }
+  const float sx = fmaf(-u, m0, mx), sy = fmaf(-v, m0, my);                    // sum p dx, sum p dy
+  const float sxx = fmaf(-u, mx + sx, mxx), syy = fmaf(-v, my + sy, myy);      // sum p dx^2, sum p dy^2
+  const float sxy = fmaf(-u, my, fmaf(-v, sx, mxy));                           // sum p dx dy
+  a[0] = r0;
+  a[1] = r1;
+  a[2] = r2;
+  a[3] = m0 / co.w;
+  a[4] = -0.5f * sxx;
+  a[5] = -sxy;
+  a[6] = -0.5f * syy;
+  a[7] = co.x * sx + co.y * sy;
+  a[8] = co.y * sx + co.z * sy;
+}
+
+// Adds the gradients of the staged entries [0, cnt) to the Gaussians', neighbouring lanes taking
+// neighbouring addresses.  Entries that no pixel blended hold zeros and are left out.
+__device__ __forceinline__ void flush_entries(const BackwardJob &J, const SumShared &sm, int cnt) {
+  const int t = fresh(threadIdx.x);
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    const int i = t + q * kBlock;
+    if (i < 3 * cnt) {
+      const int e = i / 3, f = i - 3 * e;
+      const size_t g = sm.g[e];
+      const float a = sm.acc[e * kTerms + f], b = sm.acc[e * kTerms + 4 + f];
+      if (a != 0.0f) unsafeAtomicAdd(J.g_rgb + 3 * g + f, a);
+      if (b != 0.0f) unsafeAtomicAdd(J.g_conic + 3 * g + f, b);
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int i = t + q * kBlock;
+    if (i < 2 * cnt) {
+      const float a = sm.acc[(i >> 1) * kTerms + 7 + (i & 1)];
+      if (a != 0.0f) unsafeAtomicAdd(J.g_xy + 2 * (size_t)sm.g[i >> 1] + (i & 1), a);
+    }
+  }
   if (t < cnt) {
-    const uint32_t g = J.vals[cs + t];
-    const double2 m = J.xy[g];
-    const float4 co = J.conic[g];
-    const float4 cl = J.rgb[g];
-    sm.a[t] = make_float4((float)(m.x - ox), (float)(m.y - oy), -0.5f * kLog2e * co.x, -kLog2e * co.y);
-    sm.b[t] = make_float4(-0.5f * kLog2e * co.z, __log2f(co.w), cl.x, cl.y);
-    sm.c[t] = make_float4(cl.z, co.x, co.y, co.z);
-    sm.d[t] = make_float2(1.0f / co.w, __uint_as_float(g));
+    const float a = sm.acc[t * kTerms + 3];
+    if (a != 0.0f) unsafeAtomicAdd(J.g_op + sm.g[t], a);
   }
 }
 
-__global__ __launch_bounds__(kBlock) void k_raster_backward(BackwardJob J) {
+// This lane's pixel in the back-to-front walk.
+struct PixelBack {
+  float T;             // transmittance behind the row reached
+  float s;             // g . (colour the rows behind it and the background add)
+  float g0, g1, g2;    // upstream gradient
+  bool bad;            // it is not finite
+};
+
+__device__ __forceinline__ PixelBack pixel_back(const BackwardJob &J, int ox, int oy, int px, int py, bool inside,
+                                                float T) {
+  const int64_t HW = (int64_t)J.W * J.H;
+  const int64_t pix = (int64_t)(oy + py) * J.W + (ox + px);
+  PixelBack b;
+  b.T = T;
+  b.g0 = inside ? J.dimage[pix] : 0.0f;
+  b.g1 = inside ? J.dimage[HW + pix] : 0.0f;
+  b.g2 = inside ? J.dimage[2 * HW + pix] : 0.0f;
+  b.bad = !(fabsf(b.g0) < INFINITY && fabsf(b.g1) < INFINITY && fabsf(b.g2) < INFINITY);
+  b.s = b.g0 * (J.bg[0] * T) + b.g1 * (J.bg[1] * T) + b.g2 * (J.bg[2] * T);
+  return b;
+}
+
+// One blended pair: steps the pixel in front of the row; *wgt = alpha T, *p = dL/dpower.
+__device__ __forceinline__ void back_step(PixelBack &b, float D, float cr, float cg, float cb, float *wgt, float *p) {
+  const float raw = __builtin_amdgcn_exp2f(D);
+  const float al = fminf(kAlphaMax, raw);
+  const float inv = __builtin_amdgcn_rcpf(1.0f - al);   // 1 - alpha >= 0.01
+  const float Ti = b.T * inv;
+  const float gc = fmaf(b.g0, cr, fmaf(b.g1, cg, b.g2 * cb));
+  *wgt = al * Ti;
+  const float dLda = fmaf(Ti, gc, -(b.s * inv));
+  *p = raw < kAlphaMax ? dLda * al : 0.0f;
+  b.s = fmaf(*wgt, gc, b.s);
+  b.T = Ti;
+}
+
+// largest value of the wave (uniform)
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v = max(v, (uint32_t)__shfl_xor((int)v, off, 64));
+  return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+}
+
+// The gradients of one (Gaussian, pixel) pair, added by this lane alone: pairs kept out of the
+// matrix products because their upstream gradient is not finite.
+__device__ __forceinline__ void direct_power_terms(const BackwardJob &J, uint32_t gi, double px, double py, float p) {
+  const size_t g = gi;
+  const double2 m = J.xy[g];
+  const float4 co = J.conic[g];
+  const float dx = (float)(px - m.x), dy = (float)(py - m.y);
+  unsafeAtomicAdd(J.g_op + g, p / co.w);
+  unsafeAtomicAdd(J.g_conic + 3 * g, -0.5f * dx * dx * p);
+  unsafeAtomicAdd(J.g_conic + 3 * g + 1, -dx * dy * p);
+  unsafeAtomicAdd(J.g_conic + 3 * g + 2, -0.5f * dy * dy * p);
+  unsafeAtomicAdd(J.g_xy + 2 * g, (co.x * dx + co.y * dy) * p);
+  unsafeAtomicAdd(J.g_xy + 2 * g + 1, (co.y * dx + co.z * dy) * p);
+}
+__device__ __forceinline__ void direct_colour_terms(const BackwardJob &J, uint32_t gi, float wgt, float g0, float g1,
+                                                    float g2) {
+  const size_t g = gi;
+  unsafeAtomicAdd(J.g_rgb + 3 * g, g0 * wgt);
+  unsafeAtomicAdd(J.g_rgb + 3 * g + 1, g1 * wgt);
+  unsafeAtomicAdd(J.g_rgb + 3 * g + 2, g2 * wgt);
+}
+
+// Adds to acc the nine sums over the wave's pixels of rows wl8[0..rows), at most 8: lines 0..7 of
+// vbuf hold their p, lines 8..15 their alpha T, one value per lane, zero where a pixel did not
+// blend the row.  special (uniform): some lane's upstream gradient is not finite; its pairs are
+// kept out of the product (0 x inf) and added singly.
+__device__ __forceinline__ void add_row_sums(const BackwardJob &J, float *vbuf, const PixelSide &s,
+                                             const uint8_t *wl8, int rows, SumShared &sm, const PixelBack &pb,
+                                             int px, int py, bool special) {
+  const int lane = threadIdx.x & 63;
+  const float4v *rp = reinterpret_cast<const float4v *>(vbuf + (lane & 15) * kVStride + 16 * (lane >> 4));
+  float4v d = {0.0f, 0.0f, 0.0f, 0.0f};
+  wave_fence();
+  if (__builtin_expect(special, 0)) {
+#pragma unroll 1
+    for (int m = 0; m < kRowBlock; ++m) {
+      const float p = vbuf[m * kVStride + lane], wgt = vbuf[(kRowBlock + m) * kVStride + lane];
+      if (pb.bad && p != 0.0f) {
+        vbuf[m * kVStride + lane] = 0.0f;
+        direct_power_terms(J, sm.g[wl8[m]], fresh(px) + 0.5, fresh(py) + 0.5, p);
+      }
+      if (pb.bad && wgt != 0.0f) direct_colour_terms(J, sm.g[wl8[m]], wgt, pb.g0, pb.g1, pb.g2);
+    }
+    wave_fence();
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const float4v f = rp[q];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) d = __builtin_amdgcn_mfma_f32_16x16x4f32(f[e], s.b[4 * q + e], d, 0, 0, 0);
+  }
+  // lane l holds column l % 16 of lines 4 (l / 16) + i
+  const int col = lane & 15, r0 = 4 * ((lane >> 4) & 1);
+  const uint32_t four = *reinterpret_cast<const uint32_t *>(wl8 + r0);
+  if (lane < 32 ? col < 6 : (col >= 6 && col < kTerms)) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (r0 + i < rows) unsafeAtomicAdd(&sm.acc[((four >> (8 * i)) & 255u) * kTerms + col], d[i]);
+  }
+  wave_fence();   // the buffer is free for the next rows
+}
+
+// ---- backward of the FP32 forward ---------------------------------------------------------
+// Two passes over the list: the forward recurrence again, in the forward rasterizer's FP32
+// arithmetic (so every cut, clamp and stop is decided the same way), for the pixel's final
+// transmittance and the end of its blended prefix, then the walk back.  The rows of a chunk
+// stay in LDS between the passes where the walk back starts in the chunk staged last.
+struct BwdShared {
+  float4 a[kBlock + 1];   // (u, v, -a/2 log2e, -b log2e): centre relative to the tile; row kBlock never blends
+  float4 b[kBlock + 1];   // (-c/2 log2e, log2 o, r, g)
+  float c[kBlock + 1];    // b
+  uint32_t alive[2][4];
+  SumShared s;
+};
+
+__global__ __launch_bounds__(kBlock, 4) void k_raster_backward(BackwardJob J, int all_rows) {
   __shared__ BwdShared sm;
-  const int tile = blockIdx.x;
+  const int tile = xcd_raster_bin((int)blockIdx.x, J.TX, J.TY);
+  if (tile < 0) return;
   const int ox = (tile % J.TX) * kTile, oy = (tile / J.TX) * kTile;
   const uint32_t start = J.ranges[2 * tile], end = J.ranges[2 * tile + 1];
+  if (start >= end) return;
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int px = (w & 1) * 8 + (lane & 7), py = (w >> 1) * 8 + (lane >> 3);
   const float X = px + 0.5f, Y = py + 0.5f;
   const bool inside = (ox + px < J.W) && (oy + py < J.H);
 
-  // pass 1: the forward recurrence
+  float eu = 0.0f, ev = 0.0f;                              // this thread's staged entry
+  float4 eco = make_float4(0.0f, 0.0f, 0.0f, 1.0f);
+  auto stage = [&](uint32_t cs, int cnt) {
+    if (t < cnt) {
+      const uint32_t g = J.vals[cs + t];
+      const double2 m = J.xy[g];
+      const float4 co = J.conic[g];
+      const float4 cl = J.rgb[g];
+      sm.a[t] = make_float4((float)(m.x - ox), (float)(m.y - oy), -0.5f * kLog2e * co.x, -kLog2e * co.y);
+      sm.b[t] = make_float4(-0.5f * kLog2e * co.z, __log2f(co.w), cl.x, cl.y);
+      sm.c[t] = cl.z;
+      sm.s.g[t] = g;
+      eu = (float)(m.x - ((double)ox + 8.0));
+      ev = (float)(m.y - ((double)oy + 8.0));
+      eco = co;
+      sm.s.qm[t] = all_rows ? (uint8_t)0xF
+                            : (uint8_t)mfma::quad_mask((float)(m.x - ((double)ox + 8.5)),
+                                                       (float)(m.y - ((double)oy + 8.5)), co.x, co.y, co.z,
+                                                       mfma::log2_opacity(co.w));
+    }
+  };
+
+  // pass 1: the forward recurrence.  stop: list position of the row that stops this pixel;
+  // wave_last (uniform): end of the longest blended prefix of the wave's pixels.
   float T = 1.0f;
   float cut = inside ? kCutLog2 : INFINITY;
-  uint32_t last = start;
-  if (t == 0) sm.last = start;
+  uint32_t stop = inside ? ~0u : start, wave_last = start;
+  if (t == 0) {
+    sm.s.last = start;
+    sm.a[kBlock] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    sm.b[kBlock] = make_float4(0.0f, -INFINITY, 0.0f, 0.0f);
+    sm.c[kBlock] = 0.0f;
+  }
+  uint32_t staged = start;   // first entry of the chunk in LDS
+  int it = 0;
   for (uint32_t cs = start; cs < end; cs += kBlock) {
     const int cnt = (int)min((uint32_t)kBlock, end - cs);
+    if (it > 0) {
+      block_sync();
+      const uint32_t *al = sm.alive[(it - 1) & 1];
+      if (!(al[0] | al[1] | al[2] | al[3])) break;
+    }
+    stage(cs, cnt);
+    staged = cs;
     block_sync();
-    stage(J, sm, cs, cnt, ox, oy);
-    if (!__syncthreads_or(cut != INFINITY)) break;
-    for (int j = 0; j < cnt; ++j) {
-      const float4 A = sm.a[j];
-      const float4 B = sm.b[j];
-      const float dx = X - A.x, dy = Y - A.y;
-      const float D = fmaf(dx, fmaf(A.z, dx, A.w * dy), fmaf(B.x * dy, dy, B.y));
-      if (D >= cut) {
-        const float al = fminf(kAlphaMax, __builtin_amdgcn_exp2f(D));
-        const float Tn = fmaf(-T, al, T);
-        if (Tn >= kTMin) {
-          T = Tn;
-          last = cs + (uint32_t)j + 1u;
-        } else {
-          cut = INFINITY;
+    const int n = mfma::wave_list(sm.s.qm, cnt, sm.s.wl[w]);
+    for (int r0 = 0; r0 < n; r0 += 64) {
+      if (__ballot(cut != INFINITY) == 0) break;
+      const int idx = r0 + lane < n ? (int)sm.s.wl[w][r0 + lane] : kBlock;
+      const int mm = min(64, n - r0);
+      for (int k = 0; k < mm; k += 4) {
+        float D[4];
+        int ri[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          ri[j] = __builtin_amdgcn_readlane(idx, k + j);
+          const float4 A = sm.a[ri[j]];
+          const float2 B = *reinterpret_cast<const float2 *>(&sm.b[ri[j]]);
+          const float dx = X - A.x, dy = Y - A.y;
+          D[j] = fmaf(dx, fmaf(A.z, dx, A.w * dy), fmaf(B.x * dy, dy, B.y));
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          if (D[j] >= cut) {
+            // T' = T (1 - alpha); a stop (T' < 1e-4) keeps T and disables the pixel, once per
+            // pixel, so its selects run only when a lane stops on this row
+            const float al = fminf(kAlphaMax, __builtin_amdgcn_exp2f(D[j]));
+            const float Tn = fmaf(-T, al, T);
+            wave_last = cs + (uint32_t)ri[j] + 1u;
+            if (__builtin_expect(__ballot(!(Tn >= kTMin)) != 0, 0)) {
+              const bool ok = Tn >= kTMin;
+              T = ok ? Tn : T;
+              stop = ok ? stop : cs + (uint32_t)ri[j];
+              cut = ok ? cut : INFINITY;
+            } else {
+              T = Tn;
+            }
+          }
         }
       }
     }
+    const uint64_t bal = __ballot(cut != INFINITY);
+    if (lane == 0) sm.alive[it & 1][w] = bal != 0;
+    ++it;
   }
+  wave_last = wave_max(wave_last);
   block_sync();
-  atomicMax(&sm.last, last);
+  if (lane == 0) atomicMax(&sm.s.last, wave_last);
   block_sync();
-  const uint32_t tile_last = sm.last;
+  const uint32_t tile_last = sm.s.last;
+  if (tile_last == start) return;
 
   // pass 2: back to front
-  const int64_t HW = (int64_t)J.W * J.H;
-  const int64_t pix = (int64_t)(oy + py) * J.W + (ox + px);
-  const float gp0 = inside ? J.dimage[pix] : 0.0f;
-  const float gp1 = inside ? J.dimage[HW + pix] : 0.0f;
-  const float gp2 = inside ? J.dimage[2 * HW + pix] : 0.0f;
-  const float bT0 = J.bg[0] * T, bT1 = J.bg[1] * T, bT2 = J.bg[2] * T;
-  float S0 = 0.0f, S1 = 0.0f, S2 = 0.0f;
-  for (uint32_t ce = tile_last; ce > start;) {
-    const int cnt = (int)min((uint32_t)kBlock, ce - start);
-    const uint32_t cs = ce - (uint32_t)cnt;
-    block_sync();
-    stage(J, sm, cs, cnt, ox, oy);
-    block_sync();
-    for (int j = cnt - 1; j >= 0; --j) {
-      const float4 A = sm.a[j];
-      const float4 B = sm.b[j];
-      const float dx = X - A.x, dy = Y - A.y;
-      const float D = fmaf(dx, fmaf(A.z, dx, A.w * dy), fmaf(B.x * dy, dy, B.y));
-      const bool act = (cs + (uint32_t)j < last) && (D >= kCutLog2);
-      if (__ballot(act) == 0) continue;
-      float v[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-      if (act) {
-        const float4 Cc = sm.c[j];
-        const float rop = sm.d[j].x;
-        const float raw = __builtin_amdgcn_exp2f(D);
-        const float al = fminf(kAlphaMax, raw);
-        const float inv = __builtin_amdgcn_rcpf(1.0f - al);   // 1 - alpha >= 0.01
-        const float Ti = T * inv;
-        const float wgt = al * Ti;
-        v[0] = gp0 * wgt;
-        v[1] = gp1 * wgt;
-        v[2] = gp2 * wgt;
-        const float dLda = gp0 * (B.z * Ti - (S0 + bT0) * inv) + gp1 * (B.w * Ti - (S1 + bT1) * inv) +
-                           gp2 * (Cc.x * Ti - (S2 + bT2) * inv);
-        const float dLdp = raw < kAlphaMax ? dLda * al : 0.0f;
-        v[3] = dLdp * rop;
-        v[4] = -0.5f * dx * dx * dLdp;
-        v[5] = -dx * dy * dLdp;
-        v[6] = -0.5f * dy * dy * dLdp;
-        v[7] = (Cc.y * dx + Cc.z * dy) * dLdp;
-        v[8] = (Cc.z * dx + Cc.w * dy) * dLdp;
-        S0 = fmaf(B.z, wgt, S0);
-        S1 = fmaf(B.w, wgt, S1);
-        S2 = fmaf(Cc.x, wgt, S2);
-        T = Ti;
-      }
-      add_terms(J, v, __float_as_uint(sm.d[j].y), lane);
+  PixelBack pb = pixel_back(J, ox, oy, px, py, inside, T);
+  const PixelSide side = pixel_side(J, ox, oy);
+  const bool special = __ballot(pb.bad) != 0;
+  float *vbuf = sm.s.v[w];
+  for (uint32_t cs = start + (tile_last - 1 - start) / kBlock * kBlock;; cs -= kBlock) {
+    const int cnt = (int)min((uint32_t)kBlock, end - cs);
+    if (cs != staged) {
+      block_sync();
+      stage(cs, cnt);
     }
-    ce = cs;
+#pragma unroll
+    for (int f = 0; f < kTerms; ++f) sm.s.acc[t * kTerms + f] = 0.0f;
+    block_sync();
+    const int rows = (int)min((uint32_t)cnt, wave_last > cs ? wave_last - cs : 0u);
+    const int lim = stop > cs ? (int)min(stop - cs, (uint32_t)kBlock) : 0;   // this pixel's rows [0, lim)
+    const int n = mfma::wave_list(sm.s.qm, rows, sm.s.wl[w]);
+    for (int r0 = ((n + kRowBlock - 1) / kRowBlock - 1) * kRowBlock; r0 >= 0; r0 -= kRowBlock) {
+      const int sl = r0 + (lane & (kRowBlock - 1));
+      const int idx = sl < n ? (int)sm.s.wl[w][sl] : kBlock;
+      bool any = false;
+#pragma unroll
+      for (int k = kRowBlock - 4; k >= 0; k -= 4) {
+        float D[4], cr[4], cg[4], cb[4];
+        int ri[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          ri[j] = __builtin_amdgcn_readlane(idx, k + j);
+          const float4 A = sm.a[ri[j]], B = sm.b[ri[j]];
+          cr[j] = B.z;
+          cg[j] = B.w;
+          cb[j] = sm.c[ri[j]];
+          const float dx = X - A.x, dy = Y - A.y;
+          D[j] = fmaf(dx, fmaf(A.z, dx, A.w * dy), fmaf(B.x * dy, dy, B.y));
+        }
+#pragma unroll
+        for (int j = 3; j >= 0; --j) {
+          float wgt = 0.0f, p = 0.0f;
+          const bool act = ri[j] < lim && D[j] >= kCutLog2;
+          any |= act;
+          if (act) back_step(pb, D[j], cr[j], cg[j], cb[j], &wgt, &p);
+          vbuf[(k + j) * kVStride + lane] = p;
+          vbuf[(kRowBlock + k + j) * kVStride + lane] = wgt;
+        }
+      }
+      if (__ballot(any) != 0)
+        add_row_sums(J, vbuf, side, sm.s.wl[w] + r0, n - r0, sm.s, pb, ox + px, oy + py, special);
+    }
+    block_sync();
+    if (t < cnt) convert_sums(sm.s.acc + t * kTerms, eu, ev, eco);
+    block_sync();
+    flush_entries(J, sm.s, cnt);
+    if (cs == start) break;
+    staged = ~0u;
+    block_sync();
   }
 }
 
 // ---- backward of the MFMA forward ------------------------------------------------------
-// The same derivative as above, for the image the tensorized forward writes: the power of each
-// (Gaussian, pixel) pair comes from the forward's own MFMA contraction (the Gaussian-side row and
-// the pixel-side operand built by the same functions, so D = log2(alpha_raw) is bit-identical to
-// the forward's and every cut, clamp and stop is decided the same way), and the forward's final
-// transmittance and blended-prefix end (GS_AUX_TFINAL, GS_AUX_LAST) replace the replay pass.
-//
-// One workgroup per tile, chunks of 256 entries from the tile's longest blended prefix back to
-// its first entry.  Each wave takes only the rows whose alpha can reach the cut in its 8x8
-// quadrant (quadrant culling, as in the forward), as 32-row MFMA blocks; after the lane swap a
-// lane holds the 32 rows' D for its pixel and walks them back to front.  A row is active for a
-// pixel when it lies before the pixel's blended-prefix end and D reaches the cut (the forward
-// blended exactly those).  The per-pair gradient terms and their wave sums and atomics are those
-// of the FP32 backward, with d = pixel centre - centre formed in the tile frame.
+// The power of each (Gaussian, pixel) pair comes from the forward's own MFMA contraction (the
+// Gaussian-side row and the pixel-side operand built by the same functions, so D =
+// log2(alpha_raw) is bit-identical to the forward's and every cut, clamp and stop is decided the
+// same way), and the forward's final transmittance and blended-prefix end (GS_AUX_TFINAL,
+// GS_AUX_LAST) replace the replay pass.  Each wave takes its rows as 32-row MFMA blocks; after
+// the lane swap a lane holds the 32 rows' D for its pixel and walks them back to front.  A row is
+// active for a pixel when it lies before the pixel's blended-prefix end and D reaches the cut
+// (the forward blended exactly those).
 template <int S>
 struct BwdMfmaShared {
   static constexpr int RS = (S == 3) ? 32 : 16;
   __align__(16) uint16_t A[kBlock * RS];   // Gaussian-side rows
-  float4 p0[kBlock];   // (u, v, conic a, conic b): centre in the tile frame
-  float4 p1[kBlock];   // (conic c, 1 / opacity, r, g)
-  float2 p2[kBlock];   // (b, Gaussian index bits)
-  uint8_t qm[kBlock];  // quadrant masks
-  uint8_t wl[4][kBlock];
-  uint32_t last;
+  float col[3][kBlock];                    // r, g, b
+  SumShared s;
 };
 
 template <int PREC, int S>
-__global__ __launch_bounds__(kBlock) void k_raster_backward_mfma(BackwardJob J, int all_rows) {
+__global__ __launch_bounds__(kBlock, S == 3 ? 3 : 4) void k_raster_backward_mfma(BackwardJob J, int all_rows) {
   using N = mfma::Narrow<PREC>;
   constexpr int RS = BwdMfmaShared<S>::RS;
   __shared__ BwdMfmaShared<S> sm;
-  const int tile = blockIdx.x;
+  const int tile = xcd_raster_bin((int)blockIdx.x, J.TX, J.TY);
+  if (tile < 0) return;
   const int ox = (tile % J.TX) * kTile, oy = (tile / J.TX) * kTile;
   const uint32_t start = J.ranges[2 * tile], len = J.ranges[2 * tile + 1] - start;
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int px = (w & 1) * 8 + (lane & 7), py = (w >> 1) * 8 + (lane >> 3);
-  const float xi = (float)(px - 8), yi = (float)(py - 8);   // pixel centre in the tile frame
   const bool inside = (ox + px < J.W) && (oy + py < J.H);
-  mfma::short8 B0, B1, B20, B21;
-  mfma::make_pixel_operand<PREC>(B0, B1, B20, B21);
-
-  const int64_t HW = (int64_t)J.W * J.H;
   const int64_t pix = (int64_t)(oy + py) * J.W + (ox + px);
-  float T = inside ? J.t_final[pix] : 1.0f;
+  const float T = inside ? J.t_final[pix] : 1.0f;
   // (a blended-prefix end beyond the tile's list cannot come from the forward; clamped so that no
   // entry outside the tile is read)
   const uint32_t last = inside ? min((uint32_t)J.last[pix], len) : 0u;
-  if (t == 0) sm.last = 0;
+  const uint32_t wave_last = wave_max(last);
+  if (t == 0) sm.s.last = 0;
   block_sync();
-  atomicMax(&sm.last, last);
+  if (lane == 0) atomicMax(&sm.s.last, wave_last);
   block_sync();
-  const uint32_t tile_last = sm.last;
+  const uint32_t tile_last = sm.s.last;
+  if (tile_last == 0) return;
 
-  const float gp0 = inside ? J.dimage[pix] : 0.0f;
-  const float gp1 = inside ? J.dimage[HW + pix] : 0.0f;
-  const float gp2 = inside ? J.dimage[2 * HW + pix] : 0.0f;
-  const float bT0 = J.bg[0] * T, bT1 = J.bg[1] * T, bT2 = J.bg[2] * T;
-  float S0 = 0.0f, S1 = 0.0f, S2 = 0.0f;
+  mfma::short8 B0, B1, B20, B21;
+  mfma::make_pixel_operand<PREC>(B0, B1, B20, B21);
+  PixelBack pb = pixel_back(J, ox, oy, px, py, inside, T);
+  const PixelSide side = pixel_side(J, ox, oy);
+  const bool special = __ballot(pb.bad) != 0;
+  float *vbuf = sm.s.v[w];
   mfma::short8 pad = {}, zero = {};
   if (lane < 32) pad[5] = (short)N::enc(-1000.0f);
 
   for (uint32_t ce = tile_last; ce > 0;) {
     const int cnt = (int)min((uint32_t)kBlock, ce);
     const uint32_t cs = ce - (uint32_t)cnt;   // positions in the tile's list
+    float eu = 0.0f, ev = 0.0f;
+    float4 eco = make_float4(0.0f, 0.0f, 0.0f, 1.0f);
     block_sync();
     if (t < cnt) {
       const uint32_t g = J.vals[start + cs + t];
       const double2 m = J.xy[g];
       const float4 co = J.conic[g];
-      const float4 cl = J.rgb[g];
       const float u = (float)(m.x - ((double)ox + 8.5)), v = (float)(m.y - ((double)oy + 8.5));
       const float l2o = mfma::log2_opacity(co.w);
       mfma::build_row<PREC, S>(&sm.A[t * RS], u, v, co.x, co.y, co.z, l2o);
-      sm.p0[t] = make_float4(u, v, co.x, co.y);
-      sm.p1[t] = make_float4(co.z, 1.0f / co.w, cl.x, cl.y);
-      sm.p2[t] = make_float2(cl.z, __uint_as_float(g));
-      sm.qm[t] = all_rows ? (uint8_t)0xF : (uint8_t)mfma::quad_mask(u, v, co.x, co.y, co.z, l2o);
+      const float4 cl = J.rgb[g];
+      sm.col[0][t] = cl.x;
+      sm.col[1][t] = cl.y;
+      sm.col[2][t] = cl.z;
+      sm.s.g[t] = g;
+      sm.s.qm[t] = all_rows ? (uint8_t)0xF : (uint8_t)mfma::quad_mask(u, v, co.x, co.y, co.z, l2o);
+      eu = (float)(m.x - ((double)ox + 8.0));
+      ev = (float)(m.y - ((double)oy + 8.0));
+      eco = co;
     }
+#pragma unroll
+    for (int f = 0; f < kTerms; ++f) sm.s.acc[t * kTerms + f] = 0.0f;
     block_sync();
-    const int n = mfma::wave_list(sm.qm, cnt, sm.wl[w]);
+    const int rows = (int)min((uint32_t)cnt, wave_last > cs ? wave_last - cs : 0u);
+    const int lim = last > cs ? (int)min(last - cs, (uint32_t)kBlock) : 0;   // this pixel's rows [0, lim)
+    const int n = mfma::wave_list(sm.s.qm, rows, sm.s.wl[w]);
     for (int blk = ((n + 31) >> 5) - 1; blk >= 0; --blk) {
       const int slot = 32 * blk + (lane & 31);
       const bool real = slot < n;
-      const int rr = real ? (int)sm.wl[w][slot] : 0;
+      const int rr = real ? (int)sm.s.wl[w][slot] : 0;
       const uint16_t *rp = sm.A + (size_t)rr * RS + 8 * (lane >> 5);
       const mfma::short8 a = real ? *reinterpret_cast<const mfma::short8 *>(rp) : pad;
       mfma::float16v z = {};
@@ -282,63 +517,50 @@ __global__ __launch_bounds__(kBlock) void k_raster_backward_mfma(BackwardJob J, 
         d0 = N::mma(a2, B20, d0);
         d1 = N::mma(a2, B21, d1);
       }
-      float D[32];
+      // the last rows first: registers 4 r .. 4 r + 3 of the two accumulators hold rows 8 r .. 8 r + 7
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        auto pr = __builtin_amdgcn_permlane32_swap(__float_as_uint(d0[j]), __float_as_uint(d1[j]), false, false);
-        D[8 * (j >> 2) + (j & 3)] = __uint_as_float(pr[0]);
-        D[8 * (j >> 2) + 4 + (j & 3)] = __uint_as_float(pr[1]);
-      }
+      for (int r = 3; r >= 0; --r) {
+        const int first = 32 * blk + kRowBlock * r;
+        if (first >= n) continue;   // (uniform)
+        float D[kRowBlock];
 #pragma unroll
-      for (int m = 31; m >= 0; --m) {
-        const int sl = 32 * blk + m;
-        if (sl >= n) continue;                      // (uniform)
-        const int ri = sm.wl[w][sl];
-        const bool act = (cs + (uint32_t)ri < last) && (D[m] >= kCutLog2);
-        if (__ballot(act) == 0) continue;
-        float v[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-        if (act) {
-          const float4 P0 = sm.p0[ri];
-          const float4 P1 = sm.p1[ri];
-          const float bcol = sm.p2[ri].x;
-          const float dx = xi - P0.x, dy = yi - P0.y;
-          const float raw = __builtin_amdgcn_exp2f(D[m]);
-          const float al = fminf(kAlphaMax, raw);
-          const float inv = __builtin_amdgcn_rcpf(1.0f - al);   // 1 - alpha >= 0.01
-          const float Ti = T * inv;
-          const float wgt = al * Ti;
-          v[0] = gp0 * wgt;
-          v[1] = gp1 * wgt;
-          v[2] = gp2 * wgt;
-          const float dLda = gp0 * (P1.z * Ti - (S0 + bT0) * inv) + gp1 * (P1.w * Ti - (S1 + bT1) * inv) +
-                             gp2 * (bcol * Ti - (S2 + bT2) * inv);
-          const float dLdp = raw < kAlphaMax ? dLda * al : 0.0f;
-          v[3] = dLdp * P1.y;
-          v[4] = -0.5f * dx * dx * dLdp;
-          v[5] = -dx * dy * dLdp;
-          v[6] = -0.5f * dy * dy * dLdp;
-          v[7] = (P0.z * dx + P0.w * dy) * dLdp;
-          v[8] = (P0.w * dx + P1.x * dy) * dLdp;
-          S0 = fmaf(P1.z, wgt, S0);
-          S1 = fmaf(P1.w, wgt, S1);
-          S2 = fmaf(bcol, wgt, S2);
-          T = Ti;
+        for (int j = 0; j < 4; ++j) {
+          auto pr = __builtin_amdgcn_permlane32_swap(__float_as_uint(d0[4 * r + j]), __float_as_uint(d1[4 * r + j]),
+                                                     false, false);
+          D[j] = __uint_as_float(pr[0]);
+          D[4 + j] = __uint_as_float(pr[1]);
         }
-        add_terms(J, v, __float_as_uint(sm.p2[ri].y), lane);
+        bool any = false;
+#pragma unroll
+        for (int m = kRowBlock - 1; m >= 0; --m) {
+          const int ri = __builtin_amdgcn_readlane(rr, kRowBlock * r + m);   // (a slot past n: D = -1000)
+          float wgt = 0.0f, p = 0.0f;
+          const bool act = ri < lim && D[m] >= kCutLog2;
+          any |= act;
+          if (act) back_step(pb, D[m], sm.col[0][ri], sm.col[1][ri], sm.col[2][ri], &wgt, &p);
+          vbuf[m * kVStride + lane] = p;
+          vbuf[(kRowBlock + m) * kVStride + lane] = wgt;
+        }
+        if (__ballot(any) != 0)
+          add_row_sums(J, vbuf, side, sm.s.wl[w] + first, n - first, sm.s, pb, ox + px, oy + py, special);
       }
     }
+    block_sync();
+    if (t < cnt) convert_sums(sm.s.acc + t * kTerms, eu, ev, eco);
+    block_sync();
+    flush_entries(J, sm.s, cnt);
     ce = cs;
   }
 }
 
 template <int PREC>
-hipError_t launch_bwd_mfma_p(const BackwardJob &j, int splits, int all_rows, unsigned tiles, hipStream_t st) {
+hipError_t launch_bwd_mfma_p(const BackwardJob &j, int splits, int all_rows, hipStream_t st) {
   switch (splits) {
-    case 1: hipLaunchKernelGGL((k_raster_backward_mfma<PREC, 1>), dim3(tiles), dim3(kBlock), 0, st, j, all_rows); break;
-    case 2: hipLaunchKernelGGL((k_raster_backward_mfma<PREC, 2>), dim3(tiles), dim3(kBlock), 0, st, j, all_rows); break;
+    case 1: hipLaunchKernelGGL((k_raster_backward_mfma<PREC, 1>), dim3(xcd_raster_grid(j.TX, j.TY)), dim3(kBlock), 0, st, j, all_rows); break;
+    case 2: hipLaunchKernelGGL((k_raster_backward_mfma<PREC, 2>), dim3(xcd_raster_grid(j.TX, j.TY)), dim3(kBlock), 0, st, j, all_rows); break;
     case 3:
       if (PREC == GS_PREC_FP16_MFMA) return hipErrorInvalidValue;
-      hipLaunchKernelGGL((k_raster_backward_mfma<PREC, 3>), dim3(tiles), dim3(kBlock), 0, st, j, all_rows);
+      hipLaunchKernelGGL((k_raster_backward_mfma<PREC, 3>), dim3(xcd_raster_grid(j.TX, j.TY)), dim3(kBlock), 0, st, j, all_rows);
       break;
     default: return hipErrorInvalidValue;
   }
@@ -350,15 +572,15 @@ hipError_t launch_bwd_mfma_p(const BackwardJob &j, int splits, int all_rows, uns
 hipError_t launch_raster_backward_mfma(const BackwardJob &j, int prec, int splits, bool all_rows, hipStream_t st) {
   const int tiles = j.TX * j.TY;
   if (tiles == 0) return hipSuccess;
-  if (prec == GS_PREC_FP16_MFMA) return launch_bwd_mfma_p<GS_PREC_FP16_MFMA>(j, splits, all_rows ? 1 : 0, tiles, st);
-  if (prec == GS_PREC_BF16_MFMA) return launch_bwd_mfma_p<GS_PREC_BF16_MFMA>(j, splits, all_rows ? 1 : 0, tiles, st);
+  if (prec == GS_PREC_FP16_MFMA) return launch_bwd_mfma_p<GS_PREC_FP16_MFMA>(j, splits, all_rows ? 1 : 0, st);
+  if (prec == GS_PREC_BF16_MFMA) return launch_bwd_mfma_p<GS_PREC_BF16_MFMA>(j, splits, all_rows ? 1 : 0, st);
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_raster_backward(const BackwardJob &j, hipStream_t st) {
+hipError_t launch_raster_backward(const BackwardJob &j, bool all_rows, hipStream_t st) {
   const int tiles = j.TX * j.TY;
   if (tiles == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_raster_backward, dim3((unsigned)tiles), dim3(kBlock), 0, st, j);
+  hipLaunchKernelGGL(k_raster_backward, dim3(xcd_raster_grid(j.TX, j.TY)), dim3(kBlock), 0, st, j, all_rows ? 1 : 0);
   return hipGetLastError();
 }
 

@@ -21,7 +21,7 @@ struct BackwardJob {
   const float *last;
 };
 
-hipError_t launch_raster_backward(const BackwardJob &j, hipStream_t st);
+hipError_t launch_raster_backward(const BackwardJob &j, bool all_rows, hipStream_t st);
 // The backward of the MFMA forward (precision GS_PREC_FP16_MFMA or GS_PREC_BF16_MFMA, 1..3
 // splits): the power from the same MFMA contraction as the forward, the forward's state in
 // place of a replay; all_rows runs every row in every quadrant (no quadrant culling).
