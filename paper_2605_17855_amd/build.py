@@ -17,8 +17,8 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libgs.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
-SOURCES = ["gs_api.hip", "gs_preprocess.hip", "gs_sort.hip", "gs_raster_fp32.hip", "gs_raster_mfma.hip", "gs_backward.hip"]
-HEADERS = ["gs_internal.hpp", "gs_backward.hpp", "gs_mfma.hpp"]
+SOURCES = ["gs_api.hip", "gs_preprocess.hip", "gs_sort.hip", "gs_blocks.hip", "gs_raster_fp32.hip", "gs_raster_mfma.hip", "gs_backward.hip"]
+HEADERS = ["gs_internal.hpp", "gs_sort.hpp", "gs_backward.hpp", "gs_mfma.hpp"]
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-I", INCLUDE, "-I", CSRC,

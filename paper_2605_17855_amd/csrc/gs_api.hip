@@ -131,8 +131,10 @@ struct Workspace {
   uint32_t *bval_alt;    // (capacity)
   uint32_t *bfirst;      // first Gaussian (depth rank) of each 1,024-entry block (capacity / 1,024 + 1)
   uint64_t nbfirst;
+  void *block;           // scratch of the two-level binning
   uint64_t *counts;      // {K, V}: packed for the one device-to-host copy; then the entry count of
-                         // the device-count bin sort (low 32 bits of counts[2])
+                         // the device-count bin sort (low 32 bits of counts[2]); counts[3]: the
+                         // two-level binning's block entries (low 32 bits)
   size_t total;
 };
 
@@ -147,7 +149,9 @@ Workspace carve(void *ws, int64_t n, uint64_t capacity) {
   };
   const uint64_t nn = (uint64_t)(n > 0 ? n : 1);
   w.scan = take(gsi::scan_tmp_bytes(n));
-  const size_t sort_bytes = gsi::radix_tmp_bytes(nn > capacity ? nn : capacity);
+  size_t sort_bytes = gsi::radix_tmp_bytes(nn > capacity ? nn : capacity);
+  const size_t block_bytes = gsi::block_radix_tmp_bytes(capacity);
+  if (block_bytes > sort_bytes) sort_bytes = block_bytes;
   const size_t depth_bytes = gsi::depth_sort_tmp_bytes(nn);
   w.sort = take(sort_bytes > depth_bytes ? sort_bytes : depth_bytes);
   w.dkey = reinterpret_cast<uint32_t *>(take(nn * 4));
@@ -161,7 +165,8 @@ Workspace carve(void *ws, int64_t n, uint64_t capacity) {
   w.bval_alt = reinterpret_cast<uint32_t *>(take((size_t)capacity * 4));
   w.nbfirst = capacity / gsi::kFirstsBlock + 1;
   w.bfirst = reinterpret_cast<uint32_t *>(take(w.nbfirst * 4));
-  w.counts = reinterpret_cast<uint64_t *>(take(3 * sizeof(uint64_t)));
+  w.block = take(gsi::block_tmp_bytes());
+  w.counts = reinterpret_cast<uint64_t *>(take(4 * sizeof(uint64_t)));
   w.total = off;
   return w;
 }
@@ -227,6 +232,18 @@ bool poll_counts(volatile uint64_t *h, uint64_t *kv) {
   }
 }
 
+// Whether the bins are made by way of 8x8-tile blocks (bin_and_sort_blocks): where the entries would
+// otherwise take two or more radix passes over the bin bits (or one over 512 digits), and there
+// are many.  Their number is not known yet; the capacity bounds it, and callers size it by the
+// scene or by earlier frames.  From 2^21 entries the shorter sort pays for the expansion's kernels
+// (1M Gaussians at 1080p, 2.0M entries: 67 -> 52 us from the binning to the ranges; 300K at
+// 979x546: 44 -> 46), under opacity-aware culling, whose masks gather the Gaussians' records in block
+// order, from 2^22 (2M at 1440p: 193 -> 164; 1M at 1080p: 61 -> 79).
+bool two_level(const gsi::Grid &g, uint64_t capacity, bool tight) {
+  return g.G <= 4 && gsi::block_count(g) <= gsi::kMaxBlocks && gsi::bits_for((uint64_t)g.nbins) > 8 &&
+         capacity > (tight ? 1ull << 22 : 1ull << 21);
+}
+
 gs_status do_bin_sort(const gs_projected *proj, int64_t n, const gs_camera *cam, const gs_options *opt,
                       const gs_bins *bins, uint64_t *n_keys, void *ws, hipStream_t st) {
   const gsi::Grid g = gsi::make_grid(cam->width, cam->height, opt->group);
@@ -242,6 +259,12 @@ gs_status do_bin_sort(const gs_projected *proj, int64_t n, const gs_camera *cam,
   volatile uint64_t *hkv = dev_counts ? nullptr : proj->host_counts;
   if (hkv) hkv[0] = hkv[1] = ~0ull;   // overwritten by the kernel
   const uint64_t nn = (uint64_t)(n > 0 ? n : 1);
+  const bool tight = (opt->flags & GS_OPT_TIGHT) != 0;
+  const bool blocks = nn > 1 && two_level(g, bins->capacity, tight);
+  const gsi::EntryCounts count{blocks && !tight ? nullptr : proj->count,
+                               blocks ? reinterpret_cast<const ushort4 *>(proj->rect) : nullptr};
+  const uint32_t *kclamp = reinterpret_cast<const uint32_t *>(w.counts + 2);   // K, or 0 above the capacity
+  uint32_t *entries = reinterpret_cast<uint32_t *>(w.counts + 3);
   GS_HIP(gsi::launch_depth_keys(proj->order, reinterpret_cast<const float4 *>(proj->rgb), proj->n_visible, nn, w.dkey,
                                 proj->offset + n, w.counts, const_cast<uint64_t *>(hkv), bins->capacity, w.sort, st));
   // from here on the kernel may be writing the counts: every exit waits for the stream first
@@ -249,20 +272,28 @@ gs_status do_bin_sort(const gs_projected *proj, int64_t n, const gs_camera *cam,
   // Gaussian needs no sort: a gathered scan of its count)
   const uint32_t *dkeys = w.dkey;
   hipError_t e = nn > 1 ? gsi::sort_depth(proj->order, proj->n_visible, nn, w.dkey, w.dkey_alt, w.dval_alt, w.dval_b,
-                                          w.sort, st, proj->count, w.dpos, w.bfirst, w.nbfirst)
+                                          w.sort, st, count, w.dpos, w.bfirst, w.nbfirst,
+                                          blocks ? entries : nullptr, kclamp)
                         : gsi::launch_scan_gather(proj->count, proj->order, w.dpos, (int64_t)nn, proj->n_visible,
                                                   w.scan, st);
   if (e != hipSuccess) {
     (void)hipStreamSynchronize(st);
     return hip_fail(e, "depth sort");
   }
+  // V and K: the counts, or upper bounds of *V_dev and *K_dev
+  auto bin = [&](uint32_t V, uint64_t K, const uint32_t *V_dev, const uint32_t *K_dev) {
+    void *masks = opt->group > 1 ? bins->masks : nullptr;
+    const uint32_t *firsts = nn > 1 ? w.bfirst : nullptr;
+    if (blocks)
+      return gsi::bin_and_sort_blocks(proj->order, dkeys, w.dpos, firsts, V, K, V_dev, K_dev, entries, proj->rect,
+                                      proj->xy, proj->conic, tight, g, w.bkey, w.bval, w.bkey_alt, w.bval_alt,
+                                      bins->ranges, masks, bins->vals, bins->keys, w.sort, w.block, st);
+    return gsi::bin_and_sort(proj->order, dkeys, w.dpos, firsts, V, K, V_dev, K_dev, proj->rect, proj->xy, proj->conic,
+                             tight, g, w.bkey, w.bval, w.bkey_alt, w.bval_alt, bins->ranges, masks, bins->vals,
+                             bins->keys, w.sort, st);
+  };
   if (dev_counts) {
-    const uint32_t *kdev = reinterpret_cast<const uint32_t *>(w.counts + 2);
-    GS_HIP(gsi::bin_and_sort(proj->order, dkeys, w.dpos, nn > 1 ? w.bfirst : nullptr, (uint32_t)nn, bins->capacity,
-                             proj->n_visible, kdev, proj->rect, proj->xy, proj->conic,
-                             (opt->flags & GS_OPT_TIGHT) != 0, g, w.bkey, w.bval, w.bkey_alt, w.bval_alt,
-                             bins->ranges, opt->group > 1 ? bins->masks : nullptr, bins->vals, bins->keys, w.sort,
-                             st));
+    GS_HIP(bin((uint32_t)nn, bins->capacity, proj->n_visible, kclamp));
     return GS_OK;
   }
   uint64_t kv[2] = {0, 0};
@@ -292,10 +323,7 @@ gs_status do_bin_sort(const gs_projected *proj, int64_t n, const gs_camera *cam,
   }
   // one thread per entry (also clears the bin ranges), the bin passes (the last one places the
   // Gaussian indices and 64-bit keys), the ranges and masks
-  GS_HIP(gsi::bin_and_sort(proj->order, dkeys, w.dpos, nn > 1 ? w.bfirst : nullptr, V, K, nullptr, nullptr, proj->rect,
-                           proj->xy, proj->conic,
-                           (opt->flags & GS_OPT_TIGHT) != 0, g, w.bkey, w.bval, w.bkey_alt, w.bval_alt, bins->ranges,
-                           opt->group > 1 ? bins->masks : nullptr, bins->vals, bins->keys, w.sort, st));
+  GS_HIP(bin(V, K, nullptr, nullptr));
   return GS_OK;
 }
 

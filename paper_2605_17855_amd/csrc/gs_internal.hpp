@@ -237,6 +237,20 @@ size_t depth_sort_tmp_bytes(uint64_t n_max);
 // reports in *in_alt whether the result ended in the alternate buffers.
 hipError_t radix_sort(uint64_t *keys, uint32_t *vals, uint64_t *keys_alt, uint32_t *vals_alt, uint64_t n, int lo,
                       int hi, void *tmp, hipStream_t st, bool *in_alt);
+// Two-level binning: entries are first binned and sorted by blocks of 8x8 tiles and then
+// expanded to the bins inside each block.
+constexpr int kBlockTiles = 8;
+constexpr uint64_t kMaxBlocks = 512;   // one radix pass of at most 512 digits
+inline uint64_t block_count(const Grid &g) { return (uint64_t)make_grid(g.W, g.H, kBlockTiles).nbins; }
+
+// Entries of a Gaussian: count[g] (its bins), or with rect the 8x8-tile blocks its footprint
+// overlaps, with both the smaller of the two (opacity-aware culling can leave fewer bins than the
+// footprint has blocks; so the block entries fit wherever the bin entries do).
+struct EntryCounts {
+  const uint32_t *count;
+  const ushort4 *rect;
+};
+
 // keys[i] = depth bits of order[i] for i < *nvis (n_max >= *nvis), counts = {*K, *nvis} (the
 // entry and visible counts side by side, for one copy to the host), the low 32 bits of counts[2]
 // = *K if *K <= capacity else 0 (the entry count the device-count bin sort takes), and in tmp
@@ -248,13 +262,13 @@ hipError_t launch_depth_keys(const uint32_t *order, const float4 *rgb, const uin
 // Sorts the visible list order[0..*nvis) stably by the depth keys in keys (four passes over
 // bits [0, 31): depths are positive), using keys_alt, vals_alt and vals_b (n_max each) as
 // scratch; the sorted depth keys end in keys.  The last pass also writes dpos[i] = the
-// entries of the Gaussians before the i-th in depth order (the exclusive scan of count[order[i]],
+// entries of the Gaussians before the i-th in depth order (the exclusive scan of `count` of order[i],
 // dpos[*nvis] = all entries) and first[b] = the i whose entries hold entry b * kFirstsBlock, for
-// b < nfirst.  n_max > 1 (otherwise nothing is done).  Reads the visible count on the device,
+// b < nfirst.  total (if set): all entries, at most *limit.  n_max > 1 (otherwise nothing is done).  Reads the visible count on the device,
 // so it can be enqueued before the host knows it.
 hipError_t sort_depth(uint32_t *order, const uint32_t *nvis, uint64_t n_max, uint32_t *keys, uint32_t *keys_alt,
-                      uint32_t *vals_alt, uint32_t *vals_b, void *tmp, hipStream_t st, const uint32_t *count,
-                      uint64_t *dpos, uint32_t *first, uint64_t nfirst);
+                      uint32_t *vals_alt, uint32_t *vals_b, void *tmp, hipStream_t st, const EntryCounts &count,
+                      uint64_t *dpos, uint32_t *first, uint64_t nfirst, uint32_t *total, const uint32_t *limit);
 // Entries of the V depth-ordered visible Gaussians (the i-th one's first entry at dpos[i];
 // dkeys[i] its depth bits) as (bin key, rank in depth order) pairs in (bkey, bval), a stable
 // sort on the bin bits ping-ponging with (bkey_alt, bval_alt) whose last pass writes the final
@@ -269,6 +283,18 @@ hipError_t bin_and_sort(const uint32_t *order, const uint32_t *dkeys, const uint
                         const uint16_t *rect, const double *xy, const float *conic, bool tight, const Grid &g,
                         uint32_t *bkey, uint32_t *bval, uint32_t *bkey_alt, uint32_t *bval_alt, uint32_t *ranges,
                         void *masks, uint32_t *vals, uint64_t *keys, void *tmp, hipStream_t st);
+// The same bins by way of 8x8-tile blocks (block_count(g) <= kMaxBlocks, g.G <= 4): dpos and
+// block_first count block entries (sort_depth weighted by EntryCounts with rect), entries_dev their
+// number on the device (at most K); block_tmp holds block_tmp_bytes() bytes, tmp also
+// block_radix_tmp_bytes(K).
+hipError_t bin_and_sort_blocks(const uint32_t *order, const uint32_t *dkeys, const uint64_t *dpos,
+                               const uint32_t *block_first, uint32_t V, uint64_t K, const uint32_t *V_dev,
+                               const uint32_t *K_dev, const uint32_t *entries_dev, const uint16_t *rect,
+                               const double *xy, const float *conic, bool tight, const Grid &g, uint32_t *bkey,
+                               uint32_t *bval, uint32_t *bkey_alt, uint32_t *bval_alt, uint32_t *ranges, void *masks,
+                               uint32_t *vals, uint64_t *keys, void *tmp, void *block_tmp, hipStream_t st);
+size_t block_tmp_bytes();
+size_t block_radix_tmp_bytes(uint64_t K);
 hipError_t launch_fill_u32(uint32_t *p, uint64_t n, uint32_t v, hipStream_t st);
 
 // ---- XCD-aware work order ---------------------------------------------------------------

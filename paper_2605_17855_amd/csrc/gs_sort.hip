@@ -23,7 +23,7 @@
 // Gaussian's first entry in depth order (the offset scan the binning needs) next to the
 // sorted keys.  (Three passes of up to 11 bits were measured slower: a 2,048-digit pass
 // costs nearly two 256-digit ones.)
-#include "gs_internal.hpp"
+#include "gs_sort.hpp"
 
 namespace gsi {
 namespace {
@@ -69,49 +69,31 @@ __device__ __forceinline__ uint64_t match_digit(uint32_t d, bool valid, int nbit
   return peers;
 }
 
-// Exclusive scan of v over the 256 threads of the workgroup (wave shuffles, one LDS
-// exchange of the four wave totals); *total = the sum.  sh4 holds 4 values.
-template <typename T>
-__device__ __forceinline__ T block_exclusive_scan_t(T v, T *sh4, T *total) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  T incl = v;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const T u = __shfl_up(incl, off, 64);
-    if (lane >= off) incl += u;
-  }
-  if (lane == 63) sh4[w] = incl;
-  block_sync();
-  T before = 0, all = 0;
-#pragma unroll
-  for (int k = 0; k < kBlock / 64; ++k) {
-    const T x = sh4[k];
-    before += k < w ? x : (T)0;
-    all += x;
-  }
-  block_sync();
-  *total = all;
-  return before + incl - v;
-}
 __device__ __forceinline__ uint32_t block_exclusive_scan_u32(uint32_t v, uint32_t *sh4, uint32_t *total) {
   return block_exclusive_scan_t<uint32_t>(v, sh4, total);
 }
 
 // Per-tile digit counts: counts[d * tiles + tile].  Keys are loaded up front (8 in flight
 // per lane) and counted with one LDS atomic each.
-// n is *n_dev when n_dev is given (the grid then covers an upper bound and the surplus
-// workgroups return at once), else n_host.
-__device__ __forceinline__ uint64_t count_of(uint64_t n_host, const uint32_t *n_dev) {
-  return n_dev ? (uint64_t)*n_dev : n_host;
+// Blocks of 8x8 tiles that a footprint overlaps.
+__device__ __forceinline__ uint32_t rect_blocks(ushort4 r) {
+  return (uint32_t)(((r.z - 1) / kBlockTiles - r.x / kBlockTiles + 1) *
+                    ((r.w - 1) / kBlockTiles - r.y / kBlockTiles + 1));
 }
 
-// Weights of the depth sort's last pass: the entry count of each key's Gaussian
-// (count[vals[i]]), summed per tile and digit into wcounts[d * tiles + tile] by the count
+// Entries of Gaussian g (EntryCounts).
+__device__ __forceinline__ uint32_t entries_of(const EntryCounts &e, uint32_t g) {
+  if (!e.rect) return e.count[g];
+  const uint32_t n = rect_blocks(e.rect[g]);
+  return e.count ? min(n, e.count[g]) : n;
+}
+
+// Weights of the depth sort's last pass: the entries of each key's Gaussian vals[i], summed per tile and digit into wcounts[d * tiles + tile] by the count
 // kernel, scanned over the tiles of each digit into wprefix (64-bit) with the digit totals in
 // wtotals.
 struct DigitWeights {
   const uint32_t *vals;
-  const uint32_t *count;
+  EntryCounts entries;
   uint32_t *wcounts;
   uint64_t *wprefix;
   uint64_t *wtotals;
@@ -145,7 +127,7 @@ __global__ __launch_bounds__(kBlock) void k_radix_count(const KT *keys, uint64_t
   }
   if (WEIGHTED) {
 #pragma unroll
-    for (int r = 0; r < kRounds; ++r) c[r] = base + (uint64_t)r * 64 + lane < n ? wt.count[c[r]] : 0u;
+    for (int r = 0; r < kRounds; ++r) c[r] = base + (uint64_t)r * 64 + lane < n ? entries_of(wt.entries, c[r]) : 0u;
   }
   block_sync();
 #pragma unroll
@@ -233,6 +215,15 @@ struct FirstEntries {
   uint64_t *dpos;
   uint32_t *first;
   uint64_t nfirst;
+  uint32_t *total;              // if set: all entries, at most *limit (32 bits, for the kernels that follow)
+  const uint32_t *limit;
+};
+
+// Chunk table of the two-level binning (start != nullptr; one pass over the block bits): before each
+// block, the entries (high word) and chunks of `chunk` entries (low word); start[digits] = all.
+struct ChunkTable {
+  uint64_t *start;
+  uint32_t chunk;
 };
 
 template <typename KT, int R, int DIG, bool WEIGHTED>
@@ -240,7 +231,7 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const KT *kin, const u
                                                           uint64_t n_host, const uint32_t *n_dev, int shift, int nbits,
                                                           uint32_t tiles_max, const uint32_t *offsets,
                                                           const uint32_t *totals, FinalOut fin, DigitWeights wt,
-                                                          FirstEntries fe) {
+                                                          FirstEntries fe, ChunkTable ct) {
   constexpr int kRounds = SortTile<R>::kRounds, kWaveTile = SortTile<R>::kWaveTile, kSortTile = SortTile<R>::kTile;
   constexpr int M = DIG / kBlock;   // digits per thread in the digit-level scans
   static_assert(DIG % kBlock == 0, "digits in whole multiples of the workgroup");
@@ -256,7 +247,10 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const KT *kin, const u
   __shared__ uint32_t s_wx[WEIGHTED ? kSortTile : 1];  // their exclusive scan
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const uint64_t n = count_of(n_host, n_dev);
-  if (WEIGHTED && n == 0 && blockIdx.x == 0 && t == 0) fe.dpos[0] = 0;   // no keys: no entries
+  if (WEIGHTED && n == 0 && blockIdx.x == 0 && t == 0) {   // no keys: no entries
+    fe.dpos[0] = 0;
+    if (fe.total) *fe.total = 0u;
+  }
   const uint32_t tile = xcd_sort_tile(blockIdx.x, (n + kSortTile - 1) / kSortTile);
   if (tile == ~0u) return;
   const uint64_t tile0 = (uint64_t)tile * kSortTile;
@@ -274,7 +268,7 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const KT *kin, const u
   }
   if (WEIGHTED) {
 #pragma unroll
-    for (int r = 0; r < kRounds; ++r) kw[r] = base + (uint64_t)r * 64 + lane < n ? wt.count[val[r]] : 0u;
+    for (int r = 0; r < kRounds; ++r) kw[r] = base + (uint64_t)r * 64 + lane < n ? entries_of(wt.entries, val[r]) : 0u;
   }
   // this thread's digits t*M .. t*M + M - 1: their totals, this tile's offsets within them and,
   // weighted, the same two of the weights
@@ -350,7 +344,25 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const KT *kin, const u
     gb += tot_d[j];
     if (WEIGHTED) wb += wtot_d[j];
   }
-  if (WEIGHTED && tile == 0 && t == 0) fe.dpos[n] = wall;
+  if (!WEIGHTED && ct.start && tile == 0) {   // (uniform)
+    uint64_t v[M], sum = 0, call;
+#pragma unroll
+    for (int j = 0; j < M; ++j) {
+      v[j] = (uint64_t)tot_d[j] << 32 | (tot_d[j] + ct.chunk - 1u) / ct.chunk;
+      sum += v[j];
+    }
+    uint64_t run = block_exclusive_scan_t<uint64_t>(sum, sh8, &call);
+#pragma unroll
+    for (int j = 0; j < M; ++j) {
+      if (t * M + j <= ndig) ct.start[t * M + j] = run;
+      run += v[j];
+    }
+    if (t == 0) ct.start[ndig] = call;
+  }
+  if (WEIGHTED && tile == 0 && t == 0) {
+    fe.dpos[n] = wall;
+    if (fe.total) *fe.total = wall < (uint64_t)*fe.limit ? (uint32_t)wall : *fe.limit;
+  }
   block_sync();
 #pragma unroll
   for (int r = 0; r < kRounds; ++r) {
@@ -499,29 +511,11 @@ __device__ __forceinline__ uint32_t local_gaussian_fixed(const uint64_t *s_pos, 
 }
 
 // The bin ranges start empty (the ranges kernel writes the non-empty ones after the sort):
-// every workgroup of the binning grid clears its grid-stride share.
+// every workgroup of the binning grid clears its grid-stride share (and, for the two-level
+// binning, of its sums).
 __device__ __forceinline__ void clear_ranges(uint32_t *ranges, uint64_t nranges) {
   for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < nranges; i += (uint64_t)gridDim.x * kBlock)
     ranges[i] = 0u;
-}
-
-// Member tiles of a group entry without culling: the rectangle of the footprint's tiles inside
-// group (gx, gy), [x0, x1) x [y0, y1) in member-tile units.  The binning packs it (x0, x1 - 1,
-// y0, y1 - 1 at 3 bits each) above the bin bits of the entry's sort key, which the bin passes
-// carry along without sorting on them, so the ranges kernel expands it into the mask without
-// gathering the Gaussian's rect again.
-constexpr int kRectDescBits = 12;
-__device__ __forceinline__ uint32_t rect_desc(ushort4 rc, int G, int gx, int gy) {
-  const int x0 = max((int)rc.x - gx * G, 0), x1 = min((int)rc.z - gx * G, G);
-  const int y0 = max((int)rc.y - gy * G, 0), y1 = min((int)rc.w - gy * G, G);
-  return (uint32_t)x0 | (uint32_t)(x1 - 1) << 3 | (uint32_t)y0 << 6 | (uint32_t)(y1 - 1) << 9;
-}
-__device__ __forceinline__ uint64_t rect_desc_mask(uint32_t desc, int G) {
-  const int x0 = desc & 7, x1 = (int)((desc >> 3) & 7) + 1, y0 = (desc >> 6) & 7, y1 = (int)((desc >> 9) & 7) + 1;
-  const uint64_t row = ((1ull << (x1 - x0)) - 1ull) << x0;   // x1 - x0 <= G <= 8
-  uint64_t m = 0;
-  for (int ly = y0; ly < y1; ++ly) m |= row << (ly * G);
-  return m;
 }
 
 // Stages the first-entry offsets of the Gaussians that own entries [e0, e0 + ITEMS) into
@@ -561,6 +555,44 @@ __device__ __forceinline__ void stage_block_gaussians(const uint64_t *dpos, cons
   block_sync();
 }
 
+// What the binning takes for block entries (two-level binning; all null otherwise): words to
+// clear and, under opacity-aware culling, the Gaussians' records.  A Gaussian with fewer entries
+// than its footprint has blocks takes the blocks the alpha-cut ellipse meets, any further entry
+// an empty member rectangle.
+struct BlockBinning {
+  uint32_t *zero;
+  uint64_t nzero;
+  const double2 *xy;
+  const float4 *conic;
+};
+constexpr uint32_t kEmptyDesc = 1u;   // x0 = 1, x1 = 1: no tile
+
+// Entry j of such a Gaussian: its j-th block, or false.  (Mostly small footprints over a block edge:
+// few blocks of few tile rows, so each is tested by its own rows.)
+__device__ __forceinline__ bool culled_block(const BlockBinning &bb, uint32_t g, ushort4 r, uint32_t j, int *gx,
+                                             int *gy) {
+  const double2 m = bb.xy[g];
+  const float4 co = bb.conic[g];
+  const TightEllipse el = tight_ellipse(m.x, m.y, co.x, co.y, co.z, co.w, r.x, r.z - 1, r.y);
+  for (int by = r.y / kBlockTiles; by <= (r.w - 1) / kBlockTiles; ++by) {
+    const int y0 = max((int)r.y, by * kBlockTiles), y1 = min((int)r.w, (by + 1) * kBlockTiles);
+    for (int bx = r.x / kBlockTiles; bx <= (r.z - 1) / kBlockTiles; ++bx) {
+      bool hit = false;
+      for (int y = y0; y < y1 && !hit; ++y) {
+        int lo, hi;
+        tight_row_span(el, y, &lo, &hi);
+        hit = lo <= hi && lo < (bx + 1) * kBlockTiles && hi >= bx * kBlockTiles;
+      }
+      if (hit && j-- == 0) {
+        *gx = bx;
+        *gy = by;
+        return true;
+      }
+    }
+  }
+  return false;
+}
+
 // The first radix pass's per-tile digit counts, taken where the keys are written (the binning
 // workgroup covers exactly one sort tile, in the sort's XCD-aware tile order):
 // counts[d * tiles + tile] for the digit bits [0, nbits0).
@@ -580,7 +612,7 @@ __global__ __launch_bounds__(kBlock) void k_binning(const uint32_t *order, const
                                                     uint64_t K_host, const uint32_t *nvis_dev, const uint32_t *K_dev,
                                                     const ushort4 *rect, int G, int GX, int desc_shift,
                                                     uint32_t *bin_keys, uint32_t *vals, uint32_t *ranges,
-                                                    uint64_t nranges, FirstCounts fc) {
+                                                    uint64_t nranges, FirstCounts fc, BlockBinning bb) {
   constexpr int NI = ITEMS / kBlock;
   __shared__ uint64_t s_pos[ITEMS + 1];
   __shared__ uint32_t s_g[ITEMS];
@@ -591,6 +623,7 @@ __global__ __launch_bounds__(kBlock) void k_binning(const uint32_t *order, const
   const uint32_t tile = xcd_sort_tile(blockIdx.x, (K + ITEMS - 1) / ITEMS);
   const uint64_t e0 = (uint64_t)tile * ITEMS;
   clear_ranges(ranges, nranges);
+  clear_ranges(bb.zero, bb.nzero);
   if (tile == ~0u) return;
   for (int d = threadIdx.x; d < kWideDigits; d += kBlock) h[d] = 0;
   uint32_t first, span;
@@ -612,10 +645,16 @@ __global__ __launch_bounds__(kBlock) void k_binning(const uint32_t *order, const
       const uint32_t j = (uint32_t)(e - s_pos[l[it]]);
       const int gx0 = r[it].x / G, gx1 = (r[it].z - 1) / G, gy0 = r[it].y / G;
       const int wdt = gx1 - gx0 + 1;
-      const int gy = gy0 + (int)(j / (uint32_t)wdt), gx = gx0 + (int)(j % (uint32_t)wdt);
+      int gy = gy0 + (int)(j / (uint32_t)wdt), gx = gx0 + (int)(j % (uint32_t)wdt);
+      bool in = true;
+      if (bb.xy && s_pos[l[it] + 1] - s_pos[l[it]] < rect_blocks(r[it])) {
+        gx = gx0;
+        gy = gy0;
+        in = culled_block(bb, s_g[l[it]], r[it], j, &gx, &gy);
+      }
       const uint32_t bin = (uint32_t)(gy * GX + gx);
       // (desc_shift > 0: group bins without culling, the member-tile rectangle above the bin bits)
-      bin_keys[e] = desc_shift ? bin | rect_desc(r[it], G, gx, gy) << desc_shift : bin;
+      bin_keys[e] = desc_shift ? bin | (in ? rect_desc(r[it], G, gx, gy) : kEmptyDesc) << desc_shift : bin;
       vals[e] = first + l[it];   // the Gaussian's rank in depth order; the last sort pass turns it into its index
       if (fc.counts) atomicAdd(&h[bin & dmask], 1u);
     }
@@ -915,8 +954,8 @@ hipError_t radix_passes_r(KT *keys, uint32_t *vals, KT *keys_alt, uint32_t *vals
   uint32_t *vin = vals, *vout = vals_alt;
   const int width = DIG == kWideDigits ? kWideBits : pass_width(lo, hi);
   const FinalOut none{nullptr, nullptr, nullptr, nullptr};
-  const DigitWeights now{nullptr, nullptr, nullptr, nullptr, nullptr};
-  const FirstEntries nofe{nullptr, nullptr, 0};
+  const DigitWeights now{nullptr, {nullptr, nullptr}, nullptr, nullptr, nullptr};
+  const FirstEntries nofe{nullptr, nullptr, 0, nullptr, nullptr};
   for (int shift = lo; shift < hi; shift += width) {
     const int bits = (hi - shift) < width ? (hi - shift) : width;
     const bool last = shift + width >= hi;
@@ -927,7 +966,7 @@ hipError_t radix_passes_r(KT *keys, uint32_t *vals, KT *keys_alt, uint32_t *vals
                        (uint32_t)SortTile<R>::kTile, now);
     hipLaunchKernelGGL((k_radix_scatter<KT, R, DIG, false>), dim3(xcd_sort_grid(tiles)), dim3(kBlock), 0, st, kin,
                        vin, kout, vout, n, n_dev, shift, bits, tiles, counts, totals, (last && fin) ? *fin : none,
-                       now, nofe);
+                       now, nofe, ChunkTable{nullptr, 0});
     std::swap(kin, kout);
     std::swap(vin, vout);
     *in_alt = !*in_alt;
@@ -999,15 +1038,15 @@ inline DepthTmp depth_tmp(void *tmp, uint64_t tiles) {
 // vals_alt -> order, so that the sorted list ends where it started.
 template <int R>
 hipError_t depth_passes(uint32_t *order, const uint32_t *nvis, uint64_t n_max, uint32_t *keys, uint32_t *keys_alt,
-                        uint32_t *vals_alt, uint32_t *vals_b, void *tmp, hipStream_t st, const uint32_t *count,
-                        uint64_t *dpos, uint32_t *first, uint64_t nfirst) {
+                        uint32_t *vals_alt, uint32_t *vals_b, void *tmp, hipStream_t st, const EntryCounts &count,
+                        uint64_t *dpos, uint32_t *first, uint64_t nfirst, uint32_t *total, const uint32_t *limit) {
   const uint32_t tiles = (uint32_t)sort_tiles(n_max);
   const DepthTmp d = depth_tmp(tmp, tiles);
   const unsigned grid = xcd_sort_grid(tiles);
   const uint32_t tile_keys = (uint32_t)SortTile<R>::kTile;
   const FinalOut none{nullptr, nullptr, nullptr, nullptr};
-  const DigitWeights now{nullptr, nullptr, nullptr, nullptr, nullptr};
-  const FirstEntries nofe{nullptr, nullptr, 0};
+  const DigitWeights now{nullptr, {nullptr, nullptr}, nullptr, nullptr, nullptr};
+  const FirstEntries nofe{nullptr, nullptr, 0, nullptr, nullptr};
   uint32_t *kbuf[2] = {keys, keys_alt};
   uint32_t *vbuf[kDepthPasses + 1];
   vbuf[0] = vbuf[kDepthPasses] = order;
@@ -1023,7 +1062,7 @@ hipError_t depth_passes(uint32_t *order, const uint32_t *nvis, uint64_t n_max, u
                          n_max, nvis, tile_keys, now);
       hipLaunchKernelGGL((k_radix_scatter<uint32_t, R, kDigits, false>), dim3(grid), dim3(kBlock), 0, st, kin,
                          vbuf[p], kout, vbuf[p + 1], n_max, nvis, shift, kDepthWidth, tiles, d.counts, d.totals, none,
-                         now, nofe);
+                         now, nofe, ChunkTable{nullptr, 0});
     } else {
       // weighted by the Gaussians' entry counts, with the first entries and block firsts
       const DigitWeights wt{vbuf[p], count, d.wcounts, d.wprefix, d.wtotals};
@@ -1033,7 +1072,7 @@ hipError_t depth_passes(uint32_t *order, const uint32_t *nvis, uint64_t n_max, u
                          d.totals, n_max, nvis, tile_keys, wt);
       hipLaunchKernelGGL((k_radix_scatter<uint32_t, R, kDigits, true>), dim3(grid), dim3(kBlock), 0, st, kin, vbuf[p],
                          kout, vbuf[p + 1], n_max, nvis, shift, kDepthLastBits, tiles, d.counts, d.totals, none, wt,
-                         FirstEntries{dpos, first, nfirst});
+                         FirstEntries{dpos, first, nfirst, total, limit}, ChunkTable{nullptr, 0});
     }
   }
   return hipGetLastError();
@@ -1044,7 +1083,9 @@ size_t radix_tmp_bytes(uint64_t n) {
   // kSmallSort keys, 512 per 2,048-key tile above (the same 1 count per 4 keys), and the totals
   uint64_t counts = (uint64_t)kDigits * sort_tiles(n < kSmallSort ? n : kSmallSort);
   if (n > kSmallSort && (uint64_t)kWideDigits * sort_tiles(n) > counts) counts = (uint64_t)kWideDigits * sort_tiles(n);
-  return ((size_t)(counts ? counts : kDigits) + kWideDigits) * sizeof(uint32_t);
+  // (the two-level binning takes 512 digits per 2,048-key tile at any length: at most one 1,024-key
+  // tile's counts more)
+  return ((size_t)(counts ? counts : kDigits) + 2 * kWideDigits) * sizeof(uint32_t);
 }
 
 size_t depth_sort_tmp_bytes(uint64_t n) { return depth_tmp(nullptr, sort_tiles(n ? n : 1)).bytes; }
@@ -1066,14 +1107,14 @@ hipError_t launch_depth_keys(const uint32_t *order, const float4 *rgb, const uin
 }
 
 hipError_t sort_depth(uint32_t *order, const uint32_t *nvis, uint64_t n_max, uint32_t *keys, uint32_t *keys_alt,
-                      uint32_t *vals_alt, uint32_t *vals_b, void *tmp, hipStream_t st, const uint32_t *count,
-                      uint64_t *dpos, uint32_t *first, uint64_t nfirst) {
+                      uint32_t *vals_alt, uint32_t *vals_b, void *tmp, hipStream_t st, const EntryCounts &count,
+                      uint64_t *dpos, uint32_t *first, uint64_t nfirst, uint32_t *total, const uint32_t *limit) {
   if (n_max <= 1) return hipSuccess;
   if (n_max <= kSmallSort)
     return depth_passes<kSmallR>(order, nvis, n_max, keys, keys_alt, vals_alt, vals_b, tmp, st, count, dpos, first,
-                                 nfirst);
+                                 nfirst, total, limit);
   return depth_passes<kLargeR>(order, nvis, n_max, keys, keys_alt, vals_alt, vals_b, tmp, st, count, dpos, first,
-                               nfirst);
+                               nfirst, total, limit);
 }
 
 hipError_t bin_and_sort(const uint32_t *order, const uint32_t *dkeys, const uint64_t *dpos, const uint32_t *block_first,
@@ -1109,11 +1150,11 @@ hipError_t bin_and_sort(const uint32_t *order, const uint32_t *dkeys, const uint
     if (large)
       hipLaunchKernelGGL((k_binning<SortTile<kLargeR>::kTile>), dim3(grid), dim3(kBlock), 0, st, order, dpos,
                          block_first, V, K, V_dev, K_dev, r4, g.G, g.GX, desc_shift, bkey, bval, ranges, nranges,
-                         fc);
+                         fc, BlockBinning{nullptr, 0, nullptr, nullptr});
     else
       hipLaunchKernelGGL((k_binning<SortTile<kSmallR>::kTile>), dim3(grid), dim3(kBlock), 0, st, order, dpos,
                          block_first, V, K, V_dev, K_dev, r4, g.G, g.GX, desc_shift, bkey, bval, ranges, nranges,
-                         fc);
+                         fc, BlockBinning{nullptr, 0, nullptr, nullptr});
   }
   if (K <= 1) {
     // nothing to sort: the single entry's index, key and range directly
@@ -1137,6 +1178,85 @@ hipError_t bin_and_sort(const uint32_t *order, const uint32_t *dkeys, const uint
     hipLaunchKernelGGL(k_ranges_final<false>, rgrid, dim3(kBlock), 0, st, kf, K, K_dev, vals, r4, m2, c4,
                        tight ? 1 : 0, g.G, g.GX, desc_shift, ranges, masks);
   return hipGetLastError();
+}
+
+hipError_t bin_and_sort_blocks(const uint32_t *order, const uint32_t *dkeys, const uint64_t *dpos,
+                               const uint32_t *block_first, uint32_t V, uint64_t K, const uint32_t *V_dev,
+                               const uint32_t *K_dev, const uint32_t *entries_dev, const uint16_t *rect,
+                               const double *xy, const float *conic, bool tight, const Grid &g, uint32_t *bkey,
+                               uint32_t *bval, uint32_t *bkey_alt, uint32_t *bval_alt, uint32_t *ranges, void *masks,
+                               uint32_t *vals, uint64_t *keys, void *tmp, void *block_tmp, hipStream_t st) {
+  const uint64_t nranges = 2 * (uint64_t)g.nbins;
+  if (K == 0) return launch_fill_u32(ranges, nranges, 0u, st);
+  const Grid b = make_grid(g.W, g.H, kBlockTiles);
+  const ushort4 *r4 = reinterpret_cast<const ushort4 *>(rect);
+  const double2 *m2 = reinterpret_cast<const double2 *>(xy);
+  const float4 *c4 = reinterpret_cast<const float4 *>(conic);
+  // one pass over the block bits.  9 bits take the 512-digit pass
+  // (2,048-key tiles) at any length, so that its counts stay one per four keys.
+  const int hi = bits_for((uint64_t)b.nbins);
+  // (the block entries are a fifth to a tenth of the bin entries, so the larger sort tiles pay
+  // from four times as many of those)
+  const bool wide = hi > 8, large = wide || K > 4 * kSmallSort;
+  const unsigned tiles = grid_for(K, large ? SortTile<kLargeR>::kTile : SortTile<kSmallR>::kTile);
+  const unsigned grid = xcd_sort_grid(tiles);
+  uint32_t *counts = static_cast<uint32_t *>(tmp);
+  uint32_t *totals = counts + (uint64_t)(wide ? kWideDigits : kDigits) * tiles;
+  const FirstCounts fc{counts, hi, tiles};
+  const BlockTmp bt = block_tmp_layout(tmp, block_tmp, K);
+  const BlockBinning bb{bt.sums, BlockTmp::nsums(g, b), tight ? m2 : nullptr, c4};
+  const ChunkTable ct{bt.start, (uint32_t)kChunk};
+  const dim3 dg(grid), db(kBlock);
+  // V and K are upper bounds of the visible Gaussians and of the block entries *entries_dev
+  if (large)
+    hipLaunchKernelGGL((k_binning<SortTile<kLargeR>::kTile>), dg, db, 0, st, order, dpos, block_first, V, K, V_dev,
+                       entries_dev, r4, b.G, b.GX, hi, bkey, bval, ranges, nranges, fc, bb);
+  else
+    hipLaunchKernelGGL((k_binning<SortTile<kSmallR>::kTile>), dg, db, 0, st, order, dpos, block_first, V, K, V_dev,
+                       entries_dev, r4, b.G, b.GX, hi, bkey, bval, ranges, nranges, fc, bb);
+  const FinalOut none{nullptr, nullptr, nullptr, nullptr};
+  const DigitWeights now{nullptr, {nullptr, nullptr}, nullptr, nullptr, nullptr};
+  const FirstEntries nofe{nullptr, nullptr, 0, nullptr, nullptr};
+  hipLaunchKernelGGL(k_radix_digit_scan, dim3(1u << hi), db, 0, st, counts, tiles, totals, K, entries_dev,
+                     (uint32_t)(large ? SortTile<kLargeR>::kTile : SortTile<kSmallR>::kTile), now);
+  if (wide)
+    hipLaunchKernelGGL((k_radix_scatter<uint32_t, kLargeR, kWideDigits, false>), dg, db, 0, st, bkey, bval, bkey_alt,
+                       bval_alt, K, entries_dev, 0, hi, tiles, counts, totals, none, now, nofe, ct);
+  else if (large)
+    hipLaunchKernelGGL((k_radix_scatter<uint32_t, kLargeR, kDigits, false>), dg, db, 0, st, bkey, bval, bkey_alt,
+                       bval_alt, K, entries_dev, 0, hi, tiles, counts, totals, none, now, nofe, ct);
+  else
+    hipLaunchKernelGGL((k_radix_scatter<uint32_t, kSmallR, kDigits, false>), dg, db, 0, st, bkey, bval, bkey_alt,
+                       bval_alt, K, entries_dev, 0, hi, tiles, counts, totals, none, now, nofe, ct);
+  BlockExpand x;
+  x.ckey = bkey_alt;
+  x.crank = bval_alt;
+  x.mask_lo = bkey;   // the pair of work arrays that the sorted entries leave free
+  x.mask_hi = bval;
+  x.start = bt.start;
+  x.entries = entries_dev;
+  x.nb = 1 << hi;
+  x.BX = b.GX;
+  x.GX = g.GX;
+  x.GY = g.GY;
+  x.desc_shift = hi;
+  x.order = order;
+  x.dkeys = dkeys;
+  x.rect = r4;
+  x.xy = m2;
+  x.conic = c4;
+  x.sums = bt.sums;
+  x.rowsum = bt.sums + g.nbins;
+  x.ecount = bt.ecount;
+  x.desc = bt.desc;
+  x.rows = bt.rows;
+  x.K = K;
+  x.K_dev = K_dev;
+  x.ranges = ranges;
+  x.masks = masks;
+  x.vals = vals;
+  x.keys = keys;
+  return launch_block_expand(x, g.G, tight, st);
 }
 
 }  // namespace gsi

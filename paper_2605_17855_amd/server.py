@@ -202,9 +202,9 @@ class Server:
 # Backends
 # ---------------------------------------------------------------------------------------
 
-# fixed bytes per request: bin ranges (8 B per 16x16 tile) come on top of this slack for
-# alignment padding
-FIXED_BYTES = 1 << 18
+# fixed bytes per request: the two-level binning's sums and chunk tables (at most 512 blocks) and
+# slack for alignment padding; bin ranges (8 B per 16x16 tile) come on top
+FIXED_BYTES = 1 << 19
 
 
 def mask_bytes(group: int) -> int:

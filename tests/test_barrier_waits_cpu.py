@@ -1,4 +1,4 @@
-"""Every workgroup barrier of the raster and backward kernels waits for the wave's own LDS
+"""Every workgroup barrier of the raster, backward and block expansion kernels waits for the wave's own LDS
 writes first: in the gfx950 code, no path of straight-line instructions leads from an LDS write
 to a barrier, and no barrier heads a block, without `lgkmcnt(0)` between (the compiler was
 seen to leave the wait out at barriers in loop headers, for writes pending over the back edge)."""
@@ -37,7 +37,7 @@ def test_scan_finds_a_missing_wait():
     assert _unwaited("_Zf:\n ds_write_b32 v0, v1\n s_waitcnt vmcnt(0) lgkmcnt(0)\n s_barrier") == []
 
 
-@pytest.mark.parametrize("source", ["gs_raster_fp32.hip", "gs_raster_mfma.hip", "gs_backward.hip"])
+@pytest.mark.parametrize("source", ["gs_raster_fp32.hip", "gs_raster_mfma.hip", "gs_backward.hip", "gs_blocks.hip"])
 def test_barriers_wait_for_lds_writes(source, tmp_path):
     out = tmp_path / "k.s"
     r = subprocess.run([build.HIPCC, *build.FLAGS, "--offload-device-only", "-S", "-c",
