@@ -232,16 +232,17 @@ bool poll_counts(volatile uint64_t *h, uint64_t *kv) {
   }
 }
 
-// Whether the bins are made by way of 8x8-tile blocks (bin_and_sort_blocks): where the entries would
-// otherwise take two or more radix passes over the bin bits (or one over 512 digits), and there
-// are many.  Their number is not known yet; the capacity bounds it, and callers size it by the
-// scene or by earlier frames.  From 2^21 entries the shorter sort pays for the expansion's kernels
-// (1M Gaussians at 1080p, 2.0M entries: 67 -> 52 us from the binning to the ranges; 300K at
-// 979x546: 44 -> 46), under opacity-aware culling, whose masks gather the Gaussians' records in block
-// order, from 2^22 (2M at 1440p: 193 -> 164; 1M at 1080p: 61 -> 79).
+// Whether the bins are made by way of 8x8-tile blocks (bin_and_sort_blocks): where there are many
+// entries, and many tiles to sort them by (fewer take short radix passes anyway).  The entries'
+// number is not known yet; the capacity bounds it, and callers size it by the scene or by earlier
+// frames.  From 2^21 entries and 2^11 tiles the shorter sort pays for the expansion's kernels (direct
+// -> two-level, whole frames: 1M Gaussians at 1280x720 208 -> 196 us, at 2560x1440 302 -> 262;
+// 960x540, 2,040 tiles: 192 -> 197; 500K at 1280x720 equal).  Opacity-aware culling's masks gather the
+// Gaussians' records in block order, twice: from 2^22 and 2^13 (preparation only, 2M at 2560x1440 302 ->
+// 284 us; at 1920x1080, 8,160 tiles, 257 -> 273).
 bool two_level(const gsi::Grid &g, uint64_t capacity, bool tight) {
   return g.G <= 4 && gsi::block_count(g) <= gsi::kMaxBlocks && gsi::bits_for((uint64_t)g.nbins) > 8 &&
-         capacity > (tight ? 1ull << 22 : 1ull << 21);
+         g.TX * g.TY > (tight ? 1 << 13 : 1 << 11) && capacity > (tight ? 1ull << 22 : 1ull << 21);
 }
 
 gs_status do_bin_sort(const gs_projected *proj, int64_t n, const gs_camera *cam, const gs_options *opt,
