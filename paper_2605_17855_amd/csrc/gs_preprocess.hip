@@ -34,8 +34,8 @@ struct PreArgs {
   float4 *rgb;
   ushort4 *rect;
   uint32_t *count;
-  uint64_t *bsum;   // if set: per-workgroup sums of the counts and of the visible flags, the
-  uint32_t *bvis;   // tile sums of the count scan (256-value tiles)
+  uint64_t *bsum;   // if set: per-workgroup sums of the counts and of the visible flags, of 256
+  uint32_t *bvis;   // values each, for the count scan
 };
 
 template <typename T>
@@ -229,6 +229,10 @@ __device__ __forceinline__ uint32_t preprocess_one(const PreArgs &a, int64_t g) 
   return cnt;
 }
 
+// Bound by memory: a wave's lanes are neighbours in each of the 59 arrays, and any visible lane has
+// its lines read, so most of the scene's bytes move (6M Gaussians: 235 us, 6.0 TB/s).  Culling first and
+// running the visible ones compacted read no fewer lines (262 us), and so did larger workgroups or
+// several blocks in turn (2M Gaussians, 63 us: 78 to 90).
 template <int DEG>
 __global__ __launch_bounds__(kBlock) void k_preprocess(PreArgs a) {
   __shared__ uint64_t sh[4];
@@ -331,8 +335,8 @@ __global__ __launch_bounds__(kBlock) void k_scan_top(uint64_t *bsum, uint32_t *b
 }
 
 // PREFIXED: bsum/bvis already hold each tile's exclusive offset (k_scan_top ran); otherwise
-// they hold sums of `spt` consecutive groups per tile (spt = 1: the reduce pass's tile sums;
-// more: the preprocess's 256-value sums)
+// they hold `spt` sums per tile (spt = 1: the reduce pass's tile sums; more: the
+// preprocess's 256-value sums)
 template <bool GATHER, bool COMPACT, int kScanItems, bool PREFIXED>
 __global__ __launch_bounds__(kBlock) void k_scan_down(const uint32_t *in, const uint32_t *idx, int64_t n_host,
                                                       const uint32_t *n_dev, const uint64_t *bsum,
@@ -358,6 +362,7 @@ __global__ __launch_bounds__(kBlock) void k_scan_down(const uint32_t *in, const 
   } else {
     uint64_t pre = 0;
     uint32_t prev = 0;
+#pragma unroll 8
     for (int64_t j = threadIdx.x; j < (int64_t)blockIdx.x * spt; j += kBlock) {
       pre += bsum[j];
       if (COMPACT) prev += bvis[j];
@@ -383,15 +388,40 @@ __global__ __launch_bounds__(kBlock) void k_scan_down(const uint32_t *in, const 
     out[n] = pre_all + tot;
     if (COMPACT) *nvis = prev_all + totv;
   }
+  if constexpr (kScanItems > 4) {
+    // the tile's offsets go out through LDS, neighbouring lanes storing neighbouring ones (a lane's 16
+    // are 128 bytes: stored directly, 22 us for 3M values instead of 12)
+    __shared__ uint64_t s_out[kScanTile + kScanTile / kScanItems];   // a gap per lane: no bank conflicts
 #pragma unroll
-  for (int i = 0; i < kScanItems; ++i) {
-    if (base + i < n) {
-      out[base + i] = run;
-      if (COMPACT && v[i] > 0) order[runv++] = (uint32_t)(base + i);
+    for (int i = 0; i < kScanItems; ++i) {
+      if (COMPACT && base + i < n && v[i] > 0) order[runv++] = (uint32_t)(base + i);
+      s_out[threadIdx.x * (kScanItems + 1) + i] = run;
+      run += v[i];
     }
-    run += v[i];
+    block_sync();
+#pragma unroll
+    for (int i = 0; i < kScanItems; ++i) {
+      const int j = i * kBlock + threadIdx.x;
+      const int64_t p = (int64_t)blockIdx.x * kScanTile + j;
+      if (p < n) out[p] = s_out[j + j / kScanItems];
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < kScanItems; ++i) {
+      if (base + i < n) {
+        out[base + i] = run;
+        if (COMPACT && v[i] > 0) order[runv++] = (uint32_t)(base + i);
+      }
+      run += v[i];
+    }
   }
 }
+
+// The preprocess's 256-value sums serve the scan of up to this many values: its down-sweep adds up all
+// the sums before a tile, ever more of them (2M values: 10 us, against 12 + 5 with a reduce pass; at
+// 6M it would read 200 MB of sums from L2 to save the pass's 8 us).
+constexpr int64_t kMaxPreSummed = 1ll << 21;
+inline int64_t pre_sums(int64_t n) { return (n + kBlock - 1) / kBlock; }
 
 template <bool GATHER, bool COMPACT, int ITEMS>
 hipError_t scan_impl_t(const uint32_t *in, const uint32_t *idx, uint64_t *out, int64_t n, const uint32_t *n_dev,
@@ -400,8 +430,8 @@ hipError_t scan_impl_t(const uint32_t *in, const uint32_t *idx, uint64_t *out, i
   uint64_t *bsum = static_cast<uint64_t *>(tmp);
   if (presummed) {
     // the preprocess left one sum per 256 values (scan_presummed(n) holds)
-    const int64_t n256 = (n + kBlock - 1) / kBlock;
-    uint32_t *bv = reinterpret_cast<uint32_t *>(bsum + (n256 > 0 ? n256 : 1));
+    const int64_t ns = pre_sums(n);
+    uint32_t *bv = reinterpret_cast<uint32_t *>(bsum + (ns > 0 ? ns : 1));
     hipLaunchKernelGGL((k_scan_down<GATHER, COMPACT, ITEMS, false>), dim3((unsigned)(nb > 0 ? nb : 1)), dim3(kBlock),
                        0, st, in, idx, n, n_dev, bsum, bv, out, order, nvis, (int)(scan_tile<ITEMS>() / kBlock));
     return hipGetLastError();
@@ -431,7 +461,7 @@ hipError_t scan_impl(const uint32_t *in, const uint32_t *idx, uint64_t *out, int
 
 }  // namespace
 
-bool scan_presummed(int64_t n) { return n > 0 && n <= kSmallScan; }
+bool scan_presummed(int64_t n) { return n > 0 && n <= kMaxPreSummed; }
 
 hipError_t launch_preprocess(const gs_scene &s, const gs_camera &c, const Grid &g, const gs_projected &o,
                              bool tight, void *scan_tmp, hipStream_t st) {
@@ -462,7 +492,7 @@ hipError_t launch_preprocess(const gs_scene &s, const gs_camera &c, const Grid &
   a.rgb = reinterpret_cast<float4 *>(o.rgb);
   a.rect = reinterpret_cast<ushort4 *>(o.rect);
   a.count = o.count;
-  const unsigned blocks = (unsigned)((s.n + kBlock - 1) / kBlock);
+  const unsigned blocks = (unsigned)pre_sums(s.n);
   a.bsum = nullptr;
   a.bvis = nullptr;
   if (scan_tmp && scan_presummed(s.n)) {   // layout read by scan_impl_t (presummed)
@@ -485,8 +515,8 @@ size_t scan_tmp_bytes(int64_t n) {
   int64_t nb = (small + scan_tile<4>() - 1) / scan_tile<4>();
   const int64_t nb_large = (n + scan_tile<16>() - 1) / scan_tile<16>();
   if (nb_large > nb) nb = nb_large;
-  const int64_t n256 = (small + kBlock - 1) / kBlock;   // the preprocess's sums (scan_presummed)
-  if (n256 > nb) nb = n256;
+  const int64_t sums = pre_sums(n < kMaxPreSummed ? n : kMaxPreSummed);   // the preprocess's (scan_presummed)
+  if (sums > nb) nb = sums;
   return (size_t)((nb > 0 ? nb : 1) * (sizeof(uint64_t) + sizeof(uint32_t)) + 16);
 }
 
