@@ -22,7 +22,9 @@
 // per tile and digit, the entries of the keys' Gaussians, so that its scatter writes each
 // Gaussian's first entry in depth order (the offset scan the binning needs) next to the
 // sorted keys.  (Three passes of up to 11 bits were measured slower: a 2,048-digit pass
-// costs nearly two 256-digit ones.)
+// costs nearly two 256-digit ones.)  These passes are bound by their launches, about 4 us each
+// however few the keys: sorts of up to 1,024 tiles leave the scans of the first three passes out
+// (DigitRows; preparation of 2M Gaussians 302 -> 295 us, a 4K frame 106 -> 101).
 #include "gs_sort.hpp"
 
 namespace gsi {
@@ -104,14 +106,17 @@ __global__ __launch_bounds__(kBlock) void k_radix_count(const KT *keys, uint64_t
                                                         int shift, int nbits, uint32_t tiles_max, uint32_t *counts,
                                                         DigitWeights wt) {
   constexpr int kRounds = SortTile<R>::kRounds, kWaveTile = SortTile<R>::kWaveTile, kSortTile = SortTile<R>::kTile;
-  __shared__ uint32_t h[DIG];
-  __shared__ uint32_t hw[WEIGHTED ? DIG : 1];
+  // (weighted: the digits are the depths' exponents, a few of which hold all keys; 8 counters of each, for
+  // the lanes in turn, instead of atomics all on the same ones)
+  constexpr int C = WEIGHTED ? 8 : 1;
+  __shared__ uint32_t h[DIG * C / (WEIGHTED ? 2 : 1)];   // (at most 7 bits)
+  __shared__ uint32_t hw[WEIGHTED ? DIG * C / 2 : 1];
   const uint64_t n = count_of(n_host, n_dev);
   const uint32_t tile = xcd_sort_tile(blockIdx.x, (n + kSortTile - 1) / kSortTile);
   if (tile == ~0u) return;
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int ndig = 1 << nbits;
-  for (int d = t; d < ndig; d += kBlock) {
+  for (int d = t; d < ndig * C; d += kBlock) {
     h[d] = 0;
     if (WEIGHTED) hw[d] = 0;
   }
@@ -135,14 +140,21 @@ __global__ __launch_bounds__(kBlock) void k_radix_count(const KT *keys, uint64_t
     const bool valid = base + (uint64_t)r * 64 + lane < n;
     const uint32_t d = (uint32_t)(key[r] >> shift) & dmask;
     if (valid) {
-      atomicAdd(&h[d], 1u);   // (cheaper than grouping equal digits per wave first)
-      if (WEIGHTED) atomicAdd(&hw[d], c[r]);
+      const uint32_t k = d * C + (lane & (C - 1));
+      atomicAdd(&h[k], 1u);   // (cheaper than grouping equal digits per wave first)
+      if (WEIGHTED) atomicAdd(&hw[k], c[r]);
     }
   }
   block_sync();
   for (int d = t; d < ndig; d += kBlock) {
-    counts[(uint64_t)d * tiles_max + tile] = h[d];
-    if (WEIGHTED) wt.wcounts[(uint64_t)d * tiles_max + tile] = hw[d];
+    uint32_t s = 0, sw = 0;
+#pragma unroll
+    for (int k = 0; k < C; ++k) {
+      s += h[d * C + k];
+      if (WEIGHTED) sw += hw[d * C + k];
+    }
+    counts[(uint64_t)d * tiles_max + tile] = s;
+    if (WEIGHTED) wt.wcounts[(uint64_t)d * tiles_max + tile] = sw;
   }
 }
 
@@ -190,6 +202,98 @@ __global__ __launch_bounds__(kBlock) void k_radix_digit_scan(uint32_t *counts, u
   }
 }
 
+// Digit counts of a depth pass as rows, for sorts of few tiles: 16-bit counts of every group of
+// 2^gshift tiles (group[g * 256 + d]) and, with gshift > 0, of the group's tiles before each tile
+// (before[tile * 256 + d]).  A scatter workgroup adds up all the rows by itself (sum_rows), which needs
+// no scan between the count and the scatter: 200 tiles (1M Gaussians, a fifth visible) in 50 groups are
+// 25 KB to read from L2 and 2 us, in place of a launch of 4.3.
+constexpr int kRowShift = 2;
+struct DigitRows {
+  uint16_t *group;
+  uint16_t *before;
+  int gshift;
+};
+
+// Rows of 4 tiles by a workgroup of 4 x 256 threads.  (The weighted last pass is left to the scan: its
+// gathers want more workgroups than a quarter of the tiles, 9.7 us against 6.1 at 200 tiles.)
+template <int R>
+__global__ __launch_bounds__(kBlock << kRowShift) void k_count_rows(const uint32_t *keys, const uint32_t *n_dev,
+                                                                    int shift, int nbits, DigitRows rows) {
+  constexpr int kWaveTile = SortTile<R>::kWaveTile, kSortTile = SortTile<R>::kTile, kTiles = 1 << kRowShift;
+  __shared__ uint32_t h[kTiles][kDigits];
+  const uint64_t n = *n_dev;
+  const uint32_t tiles = (uint32_t)((n + kSortTile - 1) / kSortTile);
+  const uint32_t tile0 = blockIdx.x << kRowShift;
+  if (tile0 >= tiles) return;
+  const int t = threadIdx.x & (kBlock - 1), tl = threadIdx.x / kBlock, lane = t & 63, w = t >> 6;
+  h[tl][t] = 0;
+  const uint32_t dmask = (1u << nbits) - 1u;
+  const uint64_t base = (uint64_t)(tile0 + tl) * kSortTile + (uint64_t)w * kWaveTile;
+  uint32_t key[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const uint64_t i = base + (uint64_t)r * 64 + lane;
+    key[r] = i < n ? keys[i] : 0u;
+  }
+  block_sync();
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+    if (base + (uint64_t)r * 64 + lane < n) atomicAdd(&h[tl][(key[r] >> shift) & dmask], 1u);
+  block_sync();
+  uint32_t pre = 0;
+#pragma unroll
+  for (int k = 0; k < kTiles; ++k) pre += k < tl ? h[k][t] : 0u;
+  if (tile0 + tl < tiles) rows.before[(uint64_t)(tile0 + tl) * kDigits + t] = (uint16_t)pre;
+  if (tl == kTiles - 1) rows.group[(uint64_t)blockIdx.x * kDigits + t] = (uint16_t)(pre + h[tl][t]);
+}
+
+// Sums over the workgroup of the rows [0, mid) and [0, end), of this thread's digit.  Each half-wave
+// takes every eighth row, 8 loads in flight, and the halves meet in part (2 x 8 rows of sums).
+__device__ __forceinline__ void sum_rows(const uint16_t *rows, uint32_t mid, uint32_t end, uint32_t *part,
+                                         uint32_t *before, uint32_t *all) {
+  uint32_t a[8] = {}, b[8] = {};   // all rows, and those before mid
+  const uint4 *p = reinterpret_cast<const uint4 *>(rows) + (threadIdx.x & 31);
+  const int half = threadIdx.x >> 5, col = (threadIdx.x & 31) * 8;
+  for (uint32_t r = half; r < end; r += 64) {
+    uint4 v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = r + 8u * k < end ? p[(uint64_t)(r + 8u * k) * 32] : make_uint4(0, 0, 0, 0);
+#pragma unroll
+    for (int q = 0; q < 8; q += 4) {
+      uint32_t x[4] = {}, y[4] = {};   // (four rows' 16-bit pairs add up in place: a row's count is at most 2^13)
+#pragma unroll
+      for (int k = q; k < q + 4; ++k) {
+        const uint32_t u[4] = {v[k].x, v[k].y, v[k].z, v[k].w};
+        const uint32_t m = r + 8u * k < mid ? ~0u : 0u;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          x[j] += u[j];
+          y[j] += u[j] & m;
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        a[j] += (j & 1) ? x[j / 2] >> 16 : x[j / 2] & 0xffffu;
+        b[j] += (j & 1) ? y[j / 2] >> 16 : y[j / 2] & 0xffffu;
+      }
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    part[half * kDigits + col + j] = a[j];
+    part[(8 + half) * kDigits + col + j] = b[j];
+  }
+  block_sync();
+  uint32_t x = 0, y = 0;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    x += part[k * kDigits + threadIdx.x];
+    y += part[(8 + k) * kDigits + threadIdx.x];
+  }
+  *all = x;
+  *before = y;
+}
+
 // Stable scatter of one tile: ranks from per-wave digit counters; the tile's start for digit
 // d is (keys with a smaller digit) + offsets[d][tile]; keys are placed in LDS in tile-local
 // digit order and then stored so that consecutive lanes write consecutive addresses.
@@ -226,12 +330,13 @@ struct ChunkTable {
   uint32_t chunk;
 };
 
-template <typename KT, int R, int DIG, bool WEIGHTED>
+// ROWS: the counts are rows (DigitRows; 256 digits), else scanned (k_radix_digit_scan).
+template <typename KT, int R, int DIG, bool WEIGHTED, bool ROWS>
 __global__ __launch_bounds__(kBlock) void k_radix_scatter(const KT *kin, const uint32_t *vin, KT *kout, uint32_t *vout,
                                                           uint64_t n_host, const uint32_t *n_dev, int shift, int nbits,
                                                           uint32_t tiles_max, const uint32_t *offsets,
                                                           const uint32_t *totals, FinalOut fin, DigitWeights wt,
-                                                          FirstEntries fe, ChunkTable ct) {
+                                                          FirstEntries fe, ChunkTable ct, DigitRows rows) {
   constexpr int kRounds = SortTile<R>::kRounds, kWaveTile = SortTile<R>::kWaveTile, kSortTile = SortTile<R>::kTile;
   constexpr int M = DIG / kBlock;   // digits per thread in the digit-level scans
   static_assert(DIG % kBlock == 0, "digits in whole multiples of the workgroup");
@@ -274,6 +379,15 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const KT *kin, const u
   // weighted, the same two of the weights
   uint32_t tot_d[M], off_d[M];
   uint64_t wtot_d[WEIGHTED ? M : 1], woff_d[WEIGHTED ? M : 1];
+  if constexpr (ROWS) {
+    static_assert(M == 1 && DIG == kDigits && !WEIGHTED, "a digit per thread");
+    __shared__ uint32_t part[16 * kDigits];
+    const uint32_t tiles = (uint32_t)((n + kSortTile - 1) / kSortTile);
+    const uint32_t in_group = rows.gshift ? rows.before[(uint64_t)tile * kDigits + t] : 0u;
+    sum_rows(rows.group, tile >> rows.gshift, (tiles + (1u << rows.gshift) - 1u) >> rows.gshift, part, &off_d[0],
+             &tot_d[0]);
+    off_d[0] += in_group;
+  } else
 #pragma unroll
   for (int j = 0; j < M; ++j) {
     const int d = t * M + j;
@@ -442,7 +556,8 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const KT *kin, const u
 // Depth keys of the visible Gaussians (key[i] = bits(depth of order[i]), i < *nvis), the entry
 // and visible counts, and the first depth pass's per-tile digit counts (one workgroup per sort
 // tile of R x 256 keys; counts[d * tiles + tile] for the digit bits [0, nbits0)).
-template <int R>
+// ROWS: the counts as a 16-bit row per tile (DigitRows with gshift 0).
+template <int R, bool ROWS>
 __global__ __launch_bounds__(kBlock) void k_depth_keys(const uint32_t *order, const float4 *rgb, const uint32_t *nvis,
                                                        uint32_t *keys, const uint64_t *K, uint64_t *counts,
                                                        uint64_t *host_counts, uint64_t capacity, int nbits0,
@@ -485,6 +600,11 @@ __global__ __launch_bounds__(kBlock) void k_depth_keys(const uint32_t *order, co
     }
   }
   block_sync();
+  if constexpr (ROWS) {
+    static_assert(kDigits == kBlock, "a digit per thread");
+    reinterpret_cast<uint16_t *>(dcounts)[(uint64_t)tile * kDigits + threadIdx.x] = (uint16_t)h[threadIdx.x];
+    return;
+  }
   for (int d = threadIdx.x; d < ndig; d += kBlock) dcounts[(uint64_t)d * tiles + tile] = h[d];
 }
 
@@ -964,9 +1084,9 @@ hipError_t radix_passes_r(KT *keys, uint32_t *vals, KT *keys_alt, uint32_t *vals
                          n, n_dev, shift, bits, tiles, counts, now);
     hipLaunchKernelGGL(k_radix_digit_scan, dim3(1u << bits), dim3(kBlock), 0, st, counts, tiles, totals, n, n_dev,
                        (uint32_t)SortTile<R>::kTile, now);
-    hipLaunchKernelGGL((k_radix_scatter<KT, R, DIG, false>), dim3(xcd_sort_grid(tiles)), dim3(kBlock), 0, st, kin,
+    hipLaunchKernelGGL((k_radix_scatter<KT, R, DIG, false, false>), dim3(xcd_sort_grid(tiles)), dim3(kBlock), 0, st, kin,
                        vin, kout, vout, n, n_dev, shift, bits, tiles, counts, totals, (last && fin) ? *fin : none,
-                       now, nofe, ChunkTable{nullptr, 0});
+                       now, nofe, ChunkTable{nullptr, 0}, DigitRows{});
     std::swap(kin, kout);
     std::swap(vin, vout);
     *in_alt = !*in_alt;
@@ -1003,6 +1123,9 @@ constexpr int kDepthPasses = (kDepthBits + kDepthWidth - 1) / kDepthWidth;
 constexpr int kDepthLastBits = kDepthBits - (kDepthPasses - 1) * kDepthWidth;
 constexpr int kDepthLastDigits = 1 << kDepthLastBits;
 static_assert(kDepthWidth == 8 && kDepthPasses == 4 && kDepthLastBits == 7, "depth passes of 8, 8, 8 and 7 bits");
+// Sorts of up to this many tiles count in rows (DigitRows).  All of them visible, the first pass's
+// rows (one per tile) take 13 us to add up and a scan 5, and the later ones' (one per 4) 4; at a fifth, 1 us.
+constexpr uint64_t kRowTiles = 1024;
 
 // Scratch of the depth sort over tiles sort tiles (the same for every pass): per-tile digit
 // counts and digit totals, and the last pass's weights per tile and digit with their 64-bit
@@ -1051,18 +1174,34 @@ hipError_t depth_passes(uint32_t *order, const uint32_t *nvis, uint64_t n_max, u
   uint32_t *vbuf[kDepthPasses + 1];
   vbuf[0] = vbuf[kDepthPasses] = order;
   for (int p = 1; p < kDepthPasses; ++p) vbuf[p] = (p & 1) ? vals_alt : vals_b;
+  const bool in_rows = R == kSmallR || tiles <= kRowTiles;
+  static_assert(kSmallSort <= kRowTiles * SortTile<kSmallR>::kTile, "small sorts count in rows");
+  // (16-bit rows and their prefixes side by side in the room of the 32-bit counts)
+  uint16_t *r16 = reinterpret_cast<uint16_t *>(d.counts);
+  const dim3 groups((tiles + (1u << kRowShift) - 1u) >> kRowShift);
   for (int p = 0; p < kDepthPasses; ++p) {
     const int shift = p * kDepthWidth;
     uint32_t *kin = kbuf[p & 1], *kout = kbuf[(p + 1) & 1];
-    if (p + 1 < kDepthPasses) {
-      if (p > 0)   // the first pass was counted by k_depth_keys
-        hipLaunchKernelGGL((k_radix_count<uint32_t, R, kDigits, false>), dim3(grid), dim3(kBlock), 0, st, kin, n_max,
-                           nvis, shift, kDepthWidth, tiles, d.counts, now);
-      hipLaunchKernelGGL(k_radix_digit_scan, dim3(1u << kDepthWidth), dim3(kBlock), 0, st, d.counts, tiles, d.totals,
-                         n_max, nvis, tile_keys, now);
-      hipLaunchKernelGGL((k_radix_scatter<uint32_t, R, kDigits, false>), dim3(grid), dim3(kBlock), 0, st, kin,
+    if (p + 1 < kDepthPasses && in_rows) {
+      // the first pass was counted by k_depth_keys, in rows of single tiles
+      const DigitRows rows{r16, r16 + (uint64_t)kDigits * tiles, p > 0 ? kRowShift : 0};
+      if (p > 0)
+        hipLaunchKernelGGL(k_count_rows<R>, groups, dim3(kBlock << kRowShift), 0, st, kin, nvis, shift, kDepthWidth,
+                           rows);
+      hipLaunchKernelGGL((k_radix_scatter<uint32_t, R, kDigits, false, true>), dim3(grid), dim3(kBlock), 0, st, kin,
                          vbuf[p], kout, vbuf[p + 1], n_max, nvis, shift, kDepthWidth, tiles, d.counts, d.totals, none,
-                         now, nofe, ChunkTable{nullptr, 0});
+                         now, nofe, ChunkTable{nullptr, 0}, rows);
+    } else if (p + 1 < kDepthPasses) {
+      if constexpr (R != kSmallR) {
+        if (p > 0)
+          hipLaunchKernelGGL((k_radix_count<uint32_t, R, kDigits, false>), dim3(grid), dim3(kBlock), 0, st, kin, n_max,
+                             nvis, shift, kDepthWidth, tiles, d.counts, now);
+        hipLaunchKernelGGL(k_radix_digit_scan, dim3(1u << kDepthWidth), dim3(kBlock), 0, st, d.counts, tiles, d.totals,
+                           n_max, nvis, tile_keys, now);
+        hipLaunchKernelGGL((k_radix_scatter<uint32_t, R, kDigits, false, false>), dim3(grid), dim3(kBlock), 0, st, kin,
+                           vbuf[p], kout, vbuf[p + 1], n_max, nvis, shift, kDepthWidth, tiles, d.counts, d.totals,
+                           none, now, nofe, ChunkTable{nullptr, 0}, DigitRows{});
+      }
     } else {
       // weighted by the Gaussians' entry counts, with the first entries and block firsts
       const DigitWeights wt{vbuf[p], count, d.wcounts, d.wprefix, d.wtotals};
@@ -1070,9 +1209,10 @@ hipError_t depth_passes(uint32_t *order, const uint32_t *nvis, uint64_t n_max, u
                          nvis, shift, kDepthLastBits, tiles, d.counts, wt);
       hipLaunchKernelGGL(k_radix_digit_scan, dim3(1u << kDepthLastBits), dim3(kBlock), 0, st, d.counts, tiles,
                          d.totals, n_max, nvis, tile_keys, wt);
-      hipLaunchKernelGGL((k_radix_scatter<uint32_t, R, kDigits, true>), dim3(grid), dim3(kBlock), 0, st, kin, vbuf[p],
-                         kout, vbuf[p + 1], n_max, nvis, shift, kDepthLastBits, tiles, d.counts, d.totals, none, wt,
-                         FirstEntries{dpos, first, nfirst, total, limit}, ChunkTable{nullptr, 0});
+      hipLaunchKernelGGL((k_radix_scatter<uint32_t, R, kDigits, true, false>), dim3(grid), dim3(kBlock), 0, st, kin,
+                         vbuf[p], kout, vbuf[p + 1], n_max, nvis, shift, kDepthLastBits, tiles, d.counts, d.totals,
+                         none, wt, FirstEntries{dpos, first, nfirst, total, limit}, ChunkTable{nullptr, 0},
+                         DigitRows{});
     }
   }
   return hipGetLastError();
@@ -1097,12 +1237,13 @@ hipError_t launch_depth_keys(const uint32_t *order, const float4 *rgb, const uin
   // pass's digit counts are taken here
   const uint32_t tiles = (uint32_t)sort_tiles(n_max ? n_max : 1);
   uint32_t *dcounts = depth_tmp(tmp, tiles).counts;
-  if (n_max <= kSmallSort)
-    hipLaunchKernelGGL((k_depth_keys<kSmallR>), dim3(xcd_sort_grid(tiles)), dim3(kBlock), 0, st, order, rgb, nvis, keys,
-                       K, counts, host_counts, capacity, kDepthWidth, dcounts, tiles);
-  else
-    hipLaunchKernelGGL((k_depth_keys<kLargeR>), dim3(xcd_sort_grid(tiles)), dim3(kBlock), 0, st, order, rgb, nvis, keys,
-                       K, counts, host_counts, capacity, kDepthWidth, dcounts, tiles);
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(xcd_sort_grid(tiles)), dim3(kBlock), 0, st, order, rgb, nvis, keys, K, counts,
+                       host_counts, capacity, kDepthWidth, dcounts, tiles);
+  };
+  if (n_max <= kSmallSort) launch(k_depth_keys<kSmallR, true>);
+  else if (tiles <= kRowTiles) launch(k_depth_keys<kLargeR, true>);
+  else launch(k_depth_keys<kLargeR, false>);
   return hipGetLastError();
 }
 
@@ -1220,14 +1361,14 @@ hipError_t bin_and_sort_blocks(const uint32_t *order, const uint32_t *dkeys, con
   hipLaunchKernelGGL(k_radix_digit_scan, dim3(1u << hi), db, 0, st, counts, tiles, totals, K, entries_dev,
                      (uint32_t)(large ? SortTile<kLargeR>::kTile : SortTile<kSmallR>::kTile), now);
   if (wide)
-    hipLaunchKernelGGL((k_radix_scatter<uint32_t, kLargeR, kWideDigits, false>), dg, db, 0, st, bkey, bval, bkey_alt,
-                       bval_alt, K, entries_dev, 0, hi, tiles, counts, totals, none, now, nofe, ct);
+    hipLaunchKernelGGL((k_radix_scatter<uint32_t, kLargeR, kWideDigits, false, false>), dg, db, 0, st, bkey, bval, bkey_alt,
+                       bval_alt, K, entries_dev, 0, hi, tiles, counts, totals, none, now, nofe, ct, DigitRows{});
   else if (large)
-    hipLaunchKernelGGL((k_radix_scatter<uint32_t, kLargeR, kDigits, false>), dg, db, 0, st, bkey, bval, bkey_alt,
-                       bval_alt, K, entries_dev, 0, hi, tiles, counts, totals, none, now, nofe, ct);
+    hipLaunchKernelGGL((k_radix_scatter<uint32_t, kLargeR, kDigits, false, false>), dg, db, 0, st, bkey, bval, bkey_alt,
+                       bval_alt, K, entries_dev, 0, hi, tiles, counts, totals, none, now, nofe, ct, DigitRows{});
   else
-    hipLaunchKernelGGL((k_radix_scatter<uint32_t, kSmallR, kDigits, false>), dg, db, 0, st, bkey, bval, bkey_alt,
-                       bval_alt, K, entries_dev, 0, hi, tiles, counts, totals, none, now, nofe, ct);
+    hipLaunchKernelGGL((k_radix_scatter<uint32_t, kSmallR, kDigits, false, false>), dg, db, 0, st, bkey, bval, bkey_alt,
+                       bval_alt, K, entries_dev, 0, hi, tiles, counts, totals, none, now, nofe, ct, DigitRows{});
   BlockExpand x;
   x.ckey = bkey_alt;
   x.crank = bval_alt;
