@@ -90,12 +90,15 @@ __device__ __forceinline__ uint32_t entries_of(const EntryCounts &e, uint32_t g)
   return e.count ? min(n, e.count[g]) : n;
 }
 
-// Weights of the depth sort's last pass: the entries of each key's Gaussian vals[i], summed per tile and digit into wcounts[d * tiles + tile] by the count
-// kernel, scanned over the tiles of each digit into wprefix (64-bit) with the digit totals in
-// wtotals.
+// Weights of the depth sort's last pass: the entries of each key's Gaussian vals[i], gathered by the
+// count kernel and left in key order in weights[i] for the scatter (a second gather of 6M
+// Gaussians' footprints in depth order took 19 us), summed per tile and digit into
+// wcounts[d * tiles + tile], scanned over the tiles of each digit into wprefix (64-bit) with the
+// digit totals in wtotals.
 struct DigitWeights {
   const uint32_t *vals;
   EntryCounts entries;
+  uint32_t *weights;
   uint32_t *wcounts;
   uint64_t *wprefix;
   uint64_t *wtotals;
@@ -140,6 +143,7 @@ __global__ __launch_bounds__(kBlock) void k_radix_count(const KT *keys, uint64_t
     const bool valid = base + (uint64_t)r * 64 + lane < n;
     const uint32_t d = (uint32_t)(key[r] >> shift) & dmask;
     if (valid) {
+      if (WEIGHTED) wt.weights[base + (uint64_t)r * 64 + lane] = c[r];
       const uint32_t k = d * C + (lane & (C - 1));
       atomicAdd(&h[k], 1u);   // (cheaper than grouping equal digits per wave first)
       if (WEIGHTED) atomicAdd(&hw[k], c[r]);
@@ -370,10 +374,7 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const KT *kin, const u
     const uint64_t i = base + (uint64_t)r * 64 + lane;
     key[r] = i < n ? kin[i] : (KT)0;
     val[r] = i < n ? vin[i] : 0u;
-  }
-  if (WEIGHTED) {
-#pragma unroll
-    for (int r = 0; r < kRounds; ++r) kw[r] = base + (uint64_t)r * 64 + lane < n ? entries_of(wt.entries, val[r]) : 0u;
+    kw[r] = WEIGHTED && i < n ? wt.weights[i] : 0u;
   }
   // this thread's digits t*M .. t*M + M - 1: their totals, this tile's offsets within them and,
   // weighted, the same two of the weights
@@ -1074,7 +1075,7 @@ hipError_t radix_passes_r(KT *keys, uint32_t *vals, KT *keys_alt, uint32_t *vals
   uint32_t *vin = vals, *vout = vals_alt;
   const int width = DIG == kWideDigits ? kWideBits : pass_width(lo, hi);
   const FinalOut none{nullptr, nullptr, nullptr, nullptr};
-  const DigitWeights now{nullptr, {nullptr, nullptr}, nullptr, nullptr, nullptr};
+  const DigitWeights now{nullptr, {nullptr, nullptr}, nullptr, nullptr, nullptr, nullptr};
   const FirstEntries nofe{nullptr, nullptr, 0, nullptr, nullptr};
   for (int shift = lo; shift < hi; shift += width) {
     const int bits = (hi - shift) < width ? (hi - shift) : width;
@@ -1168,7 +1169,7 @@ hipError_t depth_passes(uint32_t *order, const uint32_t *nvis, uint64_t n_max, u
   const unsigned grid = xcd_sort_grid(tiles);
   const uint32_t tile_keys = (uint32_t)SortTile<R>::kTile;
   const FinalOut none{nullptr, nullptr, nullptr, nullptr};
-  const DigitWeights now{nullptr, {nullptr, nullptr}, nullptr, nullptr, nullptr};
+  const DigitWeights now{nullptr, {nullptr, nullptr}, nullptr, nullptr, nullptr, nullptr};
   const FirstEntries nofe{nullptr, nullptr, 0, nullptr, nullptr};
   uint32_t *kbuf[2] = {keys, keys_alt};
   uint32_t *vbuf[kDepthPasses + 1];
@@ -1204,7 +1205,7 @@ hipError_t depth_passes(uint32_t *order, const uint32_t *nvis, uint64_t n_max, u
       }
     } else {
       // weighted by the Gaussians' entry counts, with the first entries and block firsts
-      const DigitWeights wt{vbuf[p], count, d.wcounts, d.wprefix, d.wtotals};
+      const DigitWeights wt{vbuf[p], count, vals_b, d.wcounts, d.wprefix, d.wtotals};   // (vals_b is free again)
       hipLaunchKernelGGL((k_radix_count<uint32_t, R, kDigits, true>), dim3(grid), dim3(kBlock), 0, st, kin, n_max,
                          nvis, shift, kDepthLastBits, tiles, d.counts, wt);
       hipLaunchKernelGGL(k_radix_digit_scan, dim3(1u << kDepthLastBits), dim3(kBlock), 0, st, d.counts, tiles,
@@ -1356,7 +1357,7 @@ hipError_t bin_and_sort_blocks(const uint32_t *order, const uint32_t *dkeys, con
     hipLaunchKernelGGL((k_binning<SortTile<kSmallR>::kTile>), dg, db, 0, st, order, dpos, block_first, V, K, V_dev,
                        entries_dev, r4, b.G, b.GX, hi, bkey, bval, ranges, nranges, fc, bb);
   const FinalOut none{nullptr, nullptr, nullptr, nullptr};
-  const DigitWeights now{nullptr, {nullptr, nullptr}, nullptr, nullptr, nullptr};
+  const DigitWeights now{nullptr, {nullptr, nullptr}, nullptr, nullptr, nullptr, nullptr};
   const FirstEntries nofe{nullptr, nullptr, 0, nullptr, nullptr};
   hipLaunchKernelGGL(k_radix_digit_scan, dim3(1u << hi), db, 0, st, counts, tiles, totals, K, entries_dev,
                      (uint32_t)(large ? SortTile<kLargeR>::kTile : SortTile<kSmallR>::kTile), now);
