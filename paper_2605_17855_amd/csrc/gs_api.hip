@@ -267,17 +267,26 @@ gs_status do_bin_sort(const gs_projected *proj, int64_t n, const gs_camera *cam,
                                blocks ? reinterpret_cast<const ushort4 *>(proj->rect) : nullptr};
   const uint32_t *kclamp = reinterpret_cast<const uint32_t *>(w.counts + 2);   // K, or 0 above the capacity
   uint32_t *entries = reinterpret_cast<uint32_t *>(w.counts + 3);
-  GS_HIP(gsi::launch_depth_keys(proj->order, reinterpret_cast<const float4 *>(proj->rgb), proj->n_visible, nn, w.dkey,
-                                proj->offset + n, w.counts, const_cast<uint64_t *>(hkv), bins->capacity, w.sort, st));
+  const float4 *rgb = reinterpret_cast<const float4 *>(proj->rgb);
+  uint64_t *hcounts = const_cast<uint64_t *>(hkv);
+  const bool one = nn > 1 && gsi::depth_sort_one(nn);
+  if (one)
+    GS_HIP(gsi::launch_depth_sort_one(proj->order, rgb, proj->n_visible, w.dkey, proj->offset + n, w.counts, hcounts,
+                                      bins->capacity, count, w.dpos, w.bfirst, w.nbfirst, blocks ? entries : nullptr,
+                                      st));
+  else
+    GS_HIP(gsi::launch_depth_keys(proj->order, rgb, proj->n_visible, nn, w.dkey, proj->offset + n, w.counts, hcounts,
+                                  bins->capacity, w.sort, st));
+  const uint32_t *dkeys = w.dkey;
   // from here on the kernel may be writing the counts: every exit waits for the stream first
   // depth bits in depth order, and the first entry of each Gaussian in that order (a single
-  // Gaussian needs no sort: a gathered scan of its count)
-  const uint32_t *dkeys = w.dkey;
-  hipError_t e = nn > 1 ? gsi::sort_depth(proj->order, proj->n_visible, nn, w.dkey, w.dkey_alt, w.dval_alt, w.dval_b,
-                                          w.sort, st, count, w.dpos, w.bfirst, w.nbfirst,
-                                          blocks ? entries : nullptr, kclamp)
-                        : gsi::launch_scan_gather(proj->count, proj->order, w.dpos, (int64_t)nn, proj->n_visible,
-                                                  w.scan, st);
+  // Gaussian needs no sort: a gathered scan of its count; up to 8,192 are sorted already)
+  hipError_t e = hipSuccess;
+  if (nn == 1)
+    e = gsi::launch_scan_gather(proj->count, proj->order, w.dpos, (int64_t)nn, proj->n_visible, w.scan, st);
+  else if (!one)
+    e = gsi::sort_depth(proj->order, proj->n_visible, nn, w.dkey, w.dkey_alt, w.dval_alt, w.dval_b, w.sort, st, count,
+                        w.dpos, w.bfirst, w.nbfirst, blocks ? entries : nullptr, kclamp);
   if (e != hipSuccess) {
     (void)hipStreamSynchronize(st);
     return hip_fail(e, "depth sort");

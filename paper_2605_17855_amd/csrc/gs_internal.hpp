@@ -266,6 +266,12 @@ hipError_t launch_depth_keys(const uint32_t *order, const float4 *rgb, const uin
 // dpos[*nvis] = all entries) and first[b] = the i whose entries hold entry b * kFirstsBlock, for
 // b < nfirst.  total (if set): all entries, at most *limit.  n_max > 1 (otherwise nothing is done).  Reads the visible count on the device,
 // so it can be enqueued before the host knows it.
+// launch_depth_keys and sort_depth in one launch, for scenes of up to 8,192 Gaussians (depth_sort_one).
+bool depth_sort_one(uint64_t n_max);
+hipError_t launch_depth_sort_one(uint32_t *order, const float4 *rgb, const uint32_t *nvis, uint32_t *keys,
+                                 const uint64_t *K, uint64_t *counts, uint64_t *host_counts, uint64_t capacity,
+                                 const EntryCounts &count, uint64_t *dpos, uint32_t *first, uint64_t nfirst,
+                                 uint32_t *total, hipStream_t st);
 hipError_t sort_depth(uint32_t *order, const uint32_t *nvis, uint64_t n_max, uint32_t *keys, uint32_t *keys_alt,
                       uint32_t *vals_alt, uint32_t *vals_b, void *tmp, hipStream_t st, const EntryCounts &count,
                       uint64_t *dpos, uint32_t *first, uint64_t nfirst, uint32_t *total, const uint32_t *limit);

@@ -609,6 +609,191 @@ __global__ __launch_bounds__(kBlock) void k_depth_keys(const uint32_t *order, co
   for (int d = threadIdx.x; d < ndig; d += kBlock) dcounts[(uint64_t)d * tiles + tile] = h[d];
 }
 
+// The whole depth sort of a small scene in one workgroup: the keys stay in LDS over the four passes and
+// the weights are scanned at the end.  The passes above are eleven launches of about 4 us, whatever
+// their size; this is bound by its own serial steps, about 5 us a pass (a frame of 4,096 Gaussians, all
+// visible, 81 -> 69 us; of 8,192, 94 -> 89, beyond which the keys outgrow one CU).
+// Each pass ranks as k_radix_scatter does, wave by wave over consecutive keys.
+constexpr int kOneR = 8;
+constexpr int kOneThreads = 1024;
+constexpr uint64_t kOneKeys = (uint64_t)kOneR * kOneThreads;
+
+__global__ __launch_bounds__(kOneThreads) void k_depth_sort_one(uint32_t *order, const float4 *rgb,
+                                                                const uint32_t *nvis, uint32_t *keys,
+                                                                const uint64_t *K, uint64_t *counts,
+                                                                uint64_t *host_counts, uint64_t capacity,
+                                                                EntryCounts entries, FirstEntries fe) {
+  constexpr int kWaves = kOneThreads / 64;
+  __shared__ uint32_t s_key[kOneKeys];
+  __shared__ uint32_t s_val[kOneKeys];
+  __shared__ uint16_t wcnt[kWaves][kDigits];
+  __shared__ uint32_t sh4[4];
+  __shared__ uint64_t sh16[kWaves];
+  __shared__ uint32_t s_and, s_or;
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const uint32_t n = *nvis;   // at most kOneKeys: the host's bound
+  uint32_t limit = 0;
+  if (t == 0) {   // (as k_depth_keys)
+    s_and = ~0u;
+    s_or = 0u;
+    const uint64_t k = *K;
+    counts[0] = k;
+    counts[1] = n;
+    limit = k <= capacity ? (uint32_t)k : 0u;
+    reinterpret_cast<uint32_t *>(counts + 2)[0] = limit;
+    if (host_counts) {
+      host_counts[0] = k;
+      host_counts[1] = n;
+    }
+  }
+  const uint32_t rounds = (n + kOneThreads - 1) / kOneThreads;   // of 64 keys per wave
+  const uint32_t base = (uint32_t)w * 64 * rounds + lane;
+  const uint64_t lt = (1ull << lane) - 1ull;
+  uint32_t key[kOneR], val[kOneR], pos[kOneR];
+#pragma unroll
+  for (int r = 0; r < kOneR; ++r) {
+    const uint32_t i = base + 64u * r;
+    val[r] = (uint32_t)r < rounds && i < n ? order[i] : 0u;
+  }
+#pragma unroll
+  for (int r = 0; r < kOneR; ++r)
+    key[r] = (uint32_t)r < rounds && base + 64u * r < n ? __float_as_uint(rgb[val[r]].w) : 0u;
+  // digits that all keys share need no pass (the depths' exponents, often)
+  uint32_t ka = ~0u, ko = 0u;
+#pragma unroll
+  for (int r = 0; r < kOneR; ++r) {
+    if ((uint32_t)r < rounds && base + 64u * r < n) {
+      ka &= key[r];
+      ko |= key[r];
+    }
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    ka &= __shfl_xor(ka, off, 64);
+    ko |= __shfl_xor(ko, off, 64);
+  }
+  block_sync();
+  if (lane == 0) {
+    atomicAnd(&s_and, ka);
+    atomicOr(&s_or, ko);
+  }
+  block_sync();
+  const uint32_t differ = s_and ^ s_or;
+  for (int shift = 0; shift < kDepthBits; shift += 8) {
+    if (((differ >> shift) & 0xffu) == 0u) continue;   // (uniform)
+    for (int i = t; i < kWaves * kDigits / 2; i += kOneThreads) reinterpret_cast<uint32_t *>(&wcnt[0][0])[i] = 0;
+    block_sync();   // (and every wave has read its keys of the pass before)
+#pragma unroll
+    for (int r = 0; r < kOneR; ++r) {
+      if ((uint32_t)r >= rounds) break;
+      const bool valid = base + 64u * r < n;
+      const uint32_t d = (key[r] >> shift) & 0xffu;
+      const uint64_t peers = match_digit(d, valid, 8);
+      const uint32_t rank = (uint32_t)__popcll(peers & lt);
+      const uint32_t old = wcnt[w][d];
+      pos[r] = old + rank;
+      // (the counters are this wave's own: see k_radix_scatter)
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      if (valid && rank == 0) wcnt[w][d] = (uint16_t)(old + (uint32_t)__popcll(peers));
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+    block_sync();
+    // the digits' starts, one digit per thread of the first four waves
+    uint32_t c[kWaves], all = 0, incl = 0;
+    if (t < kDigits) {
+#pragma unroll
+      for (int k = 0; k < kWaves; ++k) {
+        c[k] = wcnt[k][t];
+        all += c[k];
+      }
+      incl = all;
+#pragma unroll
+      for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t u = __shfl_up(incl, off, 64);
+        if (lane >= off) incl += u;
+      }
+      if (lane == 63) sh4[w] = incl;
+    }
+    block_sync();
+    if (t < kDigits) {
+      uint32_t run = incl - all;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) run += k < w ? sh4[k] : 0u;
+#pragma unroll
+      for (int k = 0; k < kWaves; ++k) {
+        wcnt[k][t] = (uint16_t)run;
+        run += c[k];
+      }
+    }
+    block_sync();
+#pragma unroll
+    for (int r = 0; r < kOneR; ++r) {
+      if ((uint32_t)r < rounds && base + 64u * r < n) {
+        const uint32_t p = wcnt[w][(key[r] >> shift) & 0xffu] + pos[r];
+        s_key[p] = key[r];
+        s_val[p] = val[r];
+      }
+    }
+    block_sync();
+#pragma unroll
+    for (int r = 0; r < kOneR; ++r) {
+      const uint32_t i = base + 64u * r;
+      key[r] = (uint32_t)r < rounds && i < n ? s_key[i] : 0u;
+      val[r] = (uint32_t)r < rounds && i < n ? s_val[i] : 0u;
+    }
+  }
+  // keys and Gaussians out; the entries before each, over consecutive keys of each lane and round
+  uint32_t ew[kOneR];
+#pragma unroll
+  for (int r = 0; r < kOneR; ++r) {
+    const uint32_t i = base + 64u * r;
+    const bool in = (uint32_t)r < rounds && i < n;
+    if (in) {
+      keys[i] = key[r];
+      order[i] = val[r];
+    }
+    ew[r] = in ? entries_of(entries, val[r]) : 0u;
+  }
+  uint64_t ex[kOneR], wave_sum = 0;   // entries of the wave's keys before each
+#pragma unroll
+  for (int r = 0; r < kOneR; ++r) {
+    uint64_t incl = ew[r];
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint64_t u = __shfl_up(incl, off, 64);
+      if (lane >= off) incl += u;
+    }
+    ex[r] = wave_sum + incl - ew[r];
+    wave_sum += __shfl(incl, 63, 64);
+  }
+  if (lane == 0) sh16[w] = wave_sum;
+  block_sync();
+  uint64_t before = 0, wall = 0;
+#pragma unroll
+  for (int k = 0; k < kWaves; ++k) {
+    const uint64_t x = sh16[k];
+    before += k < w ? x : 0ull;
+    wall += x;
+  }
+#pragma unroll
+  for (int r = 0; r < kOneR; ++r) {
+    const uint32_t i = base + 64u * r;
+    if ((uint32_t)r >= rounds || i >= n) continue;
+    const uint64_t o = before + ex[r], end = o + ew[r];
+    fe.dpos[i] = o;
+    for (uint64_t bk = (o + kFirstsBlock - 1) / kFirstsBlock; bk * kFirstsBlock < end && bk < fe.nfirst; ++bk)
+      fe.first[bk] = i;
+  }
+  if (t == 0) {
+    fe.dpos[n] = wall;
+    if (fe.total) *fe.total = wall < (uint64_t)limit ? (uint32_t)wall : limit;
+  }
+}
+
 // ---- binning: one thread per entry -------------------------------------------
 // dpos[i] = first entry of the i-th visible Gaussian in depth order (exclusive scan of its
 // bin count; dpos[V] = K).  Every visible Gaussian owns at least one entry, so a workgroup's
@@ -1245,6 +1430,17 @@ hipError_t launch_depth_keys(const uint32_t *order, const float4 *rgb, const uin
   if (n_max <= kSmallSort) launch(k_depth_keys<kSmallR, true>);
   else if (tiles <= kRowTiles) launch(k_depth_keys<kLargeR, true>);
   else launch(k_depth_keys<kLargeR, false>);
+  return hipGetLastError();
+}
+
+bool depth_sort_one(uint64_t n_max) { return n_max <= kOneKeys; }
+
+hipError_t launch_depth_sort_one(uint32_t *order, const float4 *rgb, const uint32_t *nvis, uint32_t *keys,
+                                 const uint64_t *K, uint64_t *counts, uint64_t *host_counts, uint64_t capacity,
+                                 const EntryCounts &count, uint64_t *dpos, uint32_t *first, uint64_t nfirst,
+                                 uint32_t *total, hipStream_t st) {
+  hipLaunchKernelGGL(k_depth_sort_one, dim3(1), dim3(kOneThreads), 0, st, order, rgb, nvis, keys, K, counts,
+                     host_counts, capacity, count, FirstEntries{dpos, first, nfirst, total, nullptr});
   return hipGetLastError();
 }
 

@@ -10,9 +10,9 @@ from gpu_helpers import note
 pytestmark = pytest.mark.gpu
 
 
-# 1,024-key tiles up to 2^20 Gaussians, in groups of 4 (a wave's rows: 64 tiles ungrouped, 256 grouped);
+# one workgroup up to 8,192 Gaussians; 1,024-key tiles up to 2^20 Gaussians, in groups of 4 (a wave's rows: 64 tiles ungrouped, 256 grouped);
 # 2,048-key tiles above, in rows up to 2^21
-@pytest.mark.parametrize("n", [2, 1023, 1025, 4096, 4097, 66000, 270000, (1 << 20) + 1, (1 << 21) + 1])
+@pytest.mark.parametrize("n", [2, 65, 1023, 1025, 4097, 8192, 8193, 66000, 270000, (1 << 20) + 1, (1 << 21) + 1])
 def test_depth_order_is_a_stable_sort(n):
     import torch
     note(f"depth order: n {n}")
