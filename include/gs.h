@@ -86,7 +86,7 @@ enum {
    * every pixel of the tile, so the image, T_final and the weight sum are those of the full
    * lists; entry counts and GS_AUX_NEVAL counts are smaller. */
   GS_OPT_TIGHT = 1u,
-  /* The MFMA rasterizers leave out of each 8x8 quadrant's MFMA blocks the rows whose alpha
+  /* The rasterizers and the backward passes leave out of each 8x8 quadrant's rows those whose alpha
    * cannot reach the 1/255 cut at any pixel centre of that quadrant (the test is taken with a
    * margin of 1 in q, far above its own and the split operands' rounding, so the image and
    * every aux plane are those of the full rows).  This flag makes every quadrant run every row

@@ -67,7 +67,7 @@ gs_status check_options(const gs_options *o) {
     if (o->precision == GS_PREC_FP16_MFMA && o->splits == 3)
       return fail(GS_ERR_UNSUPPORTED, "FP16 supports splits 1..2 (a third FP16 piece would be subnormal)");
   } else if (o->group == 8) {
-    return fail(GS_ERR_UNSUPPORTED, "group 8 needs an MFMA precision (the FP32 rasterizer keeps every member tile in registers)");
+    return fail(GS_ERR_UNSUPPORTED, "group 8 needs an MFMA precision (the FP32 rasterizer is built for groups 1, 2 and 4)");
   }
   if (o->aux_flags & ~(uint32_t)(GS_AUX_TFINAL | GS_AUX_WSUM | GS_AUX_NEVAL | GS_AUX_NBLEND | GS_AUX_LAST))
     return fail(GS_ERR_INVALID_ARG, "aux_flags 0x%x", o->aux_flags);
