@@ -75,8 +75,6 @@ __device__ __forceinline__ uint32_t block_exclusive_scan_u32(uint32_t v, uint32_
   return block_exclusive_scan_t<uint32_t>(v, sh4, total);
 }
 
-// Per-tile digit counts: counts[d * tiles + tile].  Keys are loaded up front (8 in flight
-// per lane) and counted with one LDS atomic each.
 // Blocks of 8x8 tiles that a footprint overlaps.
 __device__ __forceinline__ uint32_t rect_blocks(ushort4 r) {
   return (uint32_t)(((r.z - 1) / kBlockTiles - r.x / kBlockTiles + 1) *
@@ -104,6 +102,8 @@ struct DigitWeights {
   uint64_t *wtotals;
 };
 
+// Per-tile digit counts: counts[d * tiles + tile].  Keys are loaded up front (8 in flight
+// per lane) and counted with one LDS atomic each.
 template <typename KT, int R, int DIG, bool WEIGHTED>
 __global__ __launch_bounds__(kBlock) void k_radix_count(const KT *keys, uint64_t n_host, const uint32_t *n_dev,
                                                         int shift, int nbits, uint32_t tiles_max, uint32_t *counts,
