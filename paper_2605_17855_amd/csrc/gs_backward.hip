@@ -10,17 +10,19 @@
 // colour that the later Gaussians and the background add, grows by alpha_i T_i (g . c_i):
 //   dL/dalpha_i = T_i (g . c_i) - s / (1 - alpha_i),   p_i = dL/dpower_i = alpha_i dL/dalpha_i.
 //
-// Sums over pixels.  A row's nine gradients are linear in nine sums over the wave's pixels: the
-// six moments sum p (1, x, y, x^2, xy, y^2) in the tile's frame and sum alpha T g (three
-// channels).  For 8 rows at a time they are one FP32 matrix product, (8 rows of p over 8 rows of
-// alpha T) x 64 pixels by 64 pixels x (6 monomials, 3 channels of g): v_mfma_f32_16x16x4_f32,
-// FP32 in, FP32 accumulate.  Its pixel side stays in 16 registers; the row side is transposed
-// through a wave-private LDS buffer.  (p by g and alpha T by the monomials are computed too and
-// not used: the two separate 16-row products that leave them out take as many matrix
-// instructions and 21 more registers.)  The four waves of a tile add their sums in LDS
-// and one thread per entry turns the moments into gradients and adds them with hardware FP32
-// atomics, once per (entry, tile).  Wave sums by lane swaps and DPP took ~45 vector instructions
-// per row and one nine-lane global atomic per (row, quadrant).
+// Sums over pixels.  A row's nine gradients are linear in nine sums over the wave's pixels: p times
+// (1, dx, dy, dx^2, dx dy, dy^2), d the pixel's offset from the Gaussian's centre, and alpha T times
+// the three channels of g.  Both are formed for 8 rows at a time from a wave-private LDS buffer
+// that turns a lane per pixel into a lane per (row, line of 8 pixels).  The six of p are summed from
+// the offsets themselves, each lane its own line, then over the 8 lines by lane swaps.  (As a matrix
+// product with the pixels' monomials, moments about a point that all rows share, they have to be
+// shifted to each centre afterwards, which costs a splat of half a pixel at a tile's edge two to three
+// digits.)  The three of alpha T are one FP32 matrix product, (8 rows x 2 halves of the quadrant) x 32
+// pixels by 32 pixels x (3 channels x 2 halves): v_mfma_f32_16x16x4_f32, FP32 in, FP32 accumulate.
+// The four waves of a tile add their sums in LDS and one thread per entry turns them into
+// gradients and adds them with hardware FP32 atomics, once per (entry, tile).  Wave sums of every row
+// by lane swaps and DPP took ~45 vector instructions per row and one nine-lane global atomic per
+// (row, quadrant).
 #include "gs_backward.hpp"
 #include "gs_mfma.hpp"
 
@@ -29,14 +31,14 @@ namespace {
 
 typedef float float4v __attribute__((ext_vector_type(4)));
 
-constexpr int kRowBlock = 8;         // rows per matrix product
+constexpr int kRowBlock = 8;         // rows summed at a time
 constexpr int kVStride = 68;         // floats per line of the transposing buffer: conflict-free 16-byte reads
 constexpr int kTerms = 9;
 
-// LDS of both kernels' sums.  acc: per staged entry, the six moments of p and the three colour
+// LDS of both kernels' sums.  acc: per staged entry, the six sums of p and the three colour
 // sums; after the conversion, its nine gradients.
 struct SumShared {
-  __align__(16) float v[4][2 * kRowBlock * kVStride];   // wave-private: lines of p, then of alpha T
+  __align__(16) float v[4][kRowBlock * kVStride];   // wave-private: the rows' p, then their alpha T
   float acc[kBlock * kTerms];
   uint32_t g[kBlock];                               // the entries' Gaussians
   __align__(4) uint8_t wl[4][kBlock];               // each wave's row list
@@ -57,61 +59,54 @@ __device__ __forceinline__ void wave_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// This lane's share of the pixel-side operand: column n = lane % 16, pixels 16 (lane / 16) + j of
-// the wave's quadrant for j < 16.  Columns 0..5 are the monomials of the pixel (centred on the
-// tile, so |x|, |y| <= 7.5), 6..8 the channels of its upstream gradient, the others zero.  A
-// pixel whose upstream gradient is not finite has zeros there and adds its terms by itself, so
-// that it reaches only the Gaussians it blends.
+// The line of 8 pixels of the wave's quadrant that this lane sums (of row lane % 8): lines 0..3 and
+// 4..7 are the two halves of the colour product.
+__device__ __forceinline__ int sum_line(int lane) { return 4 * ((lane >> 3) & 1) + (lane >> 4); }
+
+// This lane's share of the pixel-side operand of the colour product: column n = lane % 16, pixels
+// (j, lane / 16) of the half for j < 8.  Columns 0..2 are the channels of the upstream gradient in the
+// upper half, 3..5 in the lower, the others zero.  A pixel whose upstream gradient is not finite has
+// zeros there and adds its terms by itself, so that it reaches only the Gaussians it blends.
 struct PixelSide {
-  float b[16];
+  float b[8];
 };
 
 __device__ __forceinline__ PixelSide pixel_side(const BackwardJob &J, int ox, int oy) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int n = lane & 15;
   const int64_t HW = (int64_t)J.W * J.H;
+  const int py = (w >> 1) * 8 + 4 * (n >= 3) + (lane >> 4);
   PixelSide s;
 #pragma unroll
-  for (int j = 0; j < 16; ++j) {
-    const int p = 16 * (lane >> 4) + j;
-    const int px = (w & 1) * 8 + (p & 7), py = (w >> 1) * 8 + (p >> 3);
-    const float x = (float)px - 7.5f, y = (float)py - 7.5f;
-    s.b[j] = n == 0 ? 1.0f : n == 1 ? x : n == 2 ? y : n == 3 ? x * x : n == 4 ? x * y : n == 5 ? y * y : 0.0f;
-    if (n >= 6 && n < 9 && ox + px < J.W && oy + py < J.H) {
+  for (int j = 0; j < 8; ++j) {
+    const int px = (w & 1) * 8 + j;
+    s.b[j] = 0.0f;
+    if (n < 6 && ox + px < J.W && oy + py < J.H) {
       const int64_t pix = (int64_t)(oy + py) * J.W + (ox + px);
       const float g0 = J.dimage[pix], g1 = J.dimage[HW + pix], g2 = J.dimage[2 * HW + pix];
       const bool fin = fabsf(g0) < INFINITY && fabsf(g1) < INFINITY && fabsf(g2) < INFINITY;
-      s.b[j] = !fin ? 0.0f : n == 6 ? g0 : n == 7 ? g1 : g2;
+      const int c = n % 3;
+      s.b[j] = !fin ? 0.0f : c == 0 ? g0 : c == 1 ? g1 : g2;
     }
   }
   return s;
 }
 
 // One entry's nine sums to its gradients: rgb (3), opacity, conic (3), xy (2), in place.
-// (u, v): the centre in the tile-centred frame.
-__device__ __forceinline__ void convert_sums(float *a, float u, float v, const float4 co) {
-  const float m0 = a[0], mx = a[1], my = a[2], mxx = a[3], mxy = a[4], myy = a[5];
+__device__ __forceinline__ void convert_sums(float *a, const float4 co) {
+  const float m0 = a[0], sx = a[1], sy = a[2], sxx = a[3], sxy = a[4], syy = a[5];
   const float r0 = a[6], r1 = a[7], r2 = a[8];
   // an entry that no pixel blended (its record may be anything) adds nothing
-  if (m0 == 0.0f && mx == 0.0f && my == 0.0f && mxx == 0.0f && mxy == 0.0f && myy == 0.0f) {
-    a[0] = r0;
-    a[1] = r1;
-    a[2] = r2;
-    a[6] = a[7] = a[8] = 0.0f;
-    return;
-  }
-  const float sx = fmaf(-u, m0, mx), sy = fmaf(-v, m0, my);                    // sum p dx, sum p dy
-  const float sxx = fmaf(-u, mx + sx, mxx), syy = fmaf(-v, my + sy, myy);      // sum p dx^2, sum p dy^2
-  const float sxy = fmaf(-u, my, fmaf(-v, sx, mxy));                           // sum p dx dy
+  const bool none = m0 == 0.0f && sx == 0.0f && sy == 0.0f && sxx == 0.0f && sxy == 0.0f && syy == 0.0f;
   a[0] = r0;
   a[1] = r1;
   a[2] = r2;
-  a[3] = m0 / co.w;
+  a[3] = none ? 0.0f : m0 / co.w;
   a[4] = -0.5f * sxx;
   a[5] = -sxy;
   a[6] = -0.5f * syy;
-  a[7] = co.x * sx + co.y * sy;
-  a[8] = co.y * sx + co.z * sy;
+  a[7] = none ? 0.0f : co.x * sx + co.y * sy;
+  a[8] = none ? 0.0f : co.y * sx + co.z * sy;
 }
 
 // Adds the gradients of the staged entries [0, cnt) to the Gaussians', neighbouring lanes taking
@@ -186,20 +181,8 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
 }
 
-// The gradients of one (Gaussian, pixel) pair, added by this lane alone: pairs kept out of the
-// matrix products because their upstream gradient is not finite.
-__device__ __forceinline__ void direct_power_terms(const BackwardJob &J, uint32_t gi, double px, double py, float p) {
-  const size_t g = gi;
-  const double2 m = J.xy[g];
-  const float4 co = J.conic[g];
-  const float dx = (float)(px - m.x), dy = (float)(py - m.y);
-  unsafeAtomicAdd(J.g_op + g, p / co.w);
-  unsafeAtomicAdd(J.g_conic + 3 * g, -0.5f * dx * dx * p);
-  unsafeAtomicAdd(J.g_conic + 3 * g + 1, -dx * dy * p);
-  unsafeAtomicAdd(J.g_conic + 3 * g + 2, -0.5f * dy * dy * p);
-  unsafeAtomicAdd(J.g_xy + 2 * g, (co.x * dx + co.y * dy) * p);
-  unsafeAtomicAdd(J.g_xy + 2 * g + 1, (co.y * dx + co.z * dy) * p);
-}
+// The colour gradients of one (Gaussian, pixel) pair, added by this lane alone: pairs kept out of
+// the matrix product because their upstream gradient is not finite.
 __device__ __forceinline__ void direct_colour_terms(const BackwardJob &J, uint32_t gi, float wgt, float g0, float g1,
                                                     float g2) {
   const size_t g = gi;
@@ -208,42 +191,80 @@ __device__ __forceinline__ void direct_colour_terms(const BackwardJob &J, uint32
   unsafeAtomicAdd(J.g_rgb + 3 * g + 2, g2 * wgt);
 }
 
-// Adds to acc the nine sums over the wave's pixels of rows wl8[0..rows), at most 8: lines 0..7 of
-// vbuf hold their p, lines 8..15 their alpha T, one value per lane, zero where a pixel did not
-// blend the row.  special (uniform): some lane's upstream gradient is not finite; its pairs are
-// kept out of the product (0 x inf) and added singly.
-__device__ __forceinline__ void add_row_sums(const BackwardJob &J, float *vbuf, const PixelSide &s,
-                                             const uint8_t *wl8, int rows, SumShared &sm, const PixelBack &pb,
-                                             int px, int py, bool special) {
-  const int lane = threadIdx.x & 63;
-  const float4v *rp = reinterpret_cast<const float4v *>(vbuf + (lane & 15) * kVStride + 16 * (lane >> 4));
-  float4v d = {0.0f, 0.0f, 0.0f, 0.0f};
+// Reduce-scatter steps of two registers at once.  swap32_add: lanes 0..31 get a[i] + a[i+32],
+// lanes 32..63 get b[i-32] + b[i].  swap16_add (rows of 16 lanes): row 0 gets a's rows 0 + 1,
+// row 1 b's rows 0 + 1, row 2 a's rows 2 + 3, row 3 b's rows 2 + 3.
+__device__ __forceinline__ float swap32_add(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float swap16_add(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+// v plus the lane eight further in its row of 16
+__device__ __forceinline__ float ror8_add(float v) {
+  return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xF, 0xF, false));
+}
+
+// Adds to acc the nine sums over the wave's pixels of 8 rows.  This lane's row (lane % 8) is staged
+// entry `e` (none, its p and alpha T zero, unless `valid`) with its centre at (u, v); (X0, Y0): the
+// quadrant's first pixel centre in the same frame.  Lines 0..7 of vbuf hold the rows' p and wgt[m] row
+// m's alpha T, one value per lane, zero where a pixel did not blend the row.  special (uniform):
+// some lane's upstream gradient is not finite; the colours of its pairs are kept out of the product
+// (0 x inf) and added singly.
+__device__ __forceinline__ void add_row_sums(const BackwardJob &J, float *vbuf, const PixelSide &s, SumShared &sm,
+                                             int e, bool valid, float u, float v, float X0, float Y0,
+                                             const float (&wgt)[kRowBlock], const PixelBack &pb, bool special) {
+  const int lane = threadIdx.x & 63, line = sum_line(lane);
+  float *mine = vbuf + (lane & (kRowBlock - 1)) * kVStride + 8 * line;
+  const float4v *rp = reinterpret_cast<const float4v *>(mine);
   wave_fence();
+  const float4v p0 = rp[0], p1 = rp[1];
+  wave_fence();
+#pragma unroll
+  for (int m = 0; m < kRowBlock; ++m) vbuf[m * kVStride + lane] = wgt[m];
+  wave_fence();
+  const float4v w0 = rp[0], w1 = rp[1];
+  // p (1, dx, dx^2) over the line, then dy, which it shares
+  float m0 = 0.0f, mx = 0.0f, mxx = 0.0f;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const float p = j < 4 ? p0[j & 3] : p1[j & 3], dx = (X0 + (float)j) - u, pdx = p * dx;
+    m0 += p;
+    mx += pdx;
+    mxx = fmaf(pdx, dx, mxx);
+  }
+  const float dy = (Y0 + (float)line) - v;
+  const float my = m0 * dy, mxy = mx * dy, myy = my * dy;
+  // over the lines: lane bits 5, 4 and 3
+  const float z0 = ror8_add(swap16_add(swap32_add(m0, mx), swap32_add(my, mxx)));
+  const float x2 = swap32_add(mxy, myy);
+  const float z1 = ror8_add(swap16_add(x2, x2));
+  // rows of 16 lanes: z0 holds sums 0, 2, 1, 3, z1 holds 4, 4, 5, 5
+  const int row = lane >> 4;
+  const bool second = (lane & 8) != 0;
+  const int f = second ? 4 + (row >> 1) : row == 1 ? 2 : row == 2 ? 1 : row;
+  if (valid && !(second && (row & 1))) unsafeAtomicAdd(&sm.acc[e * kTerms + f], second ? z1 : z0);
+  float4v d = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int j = 0; j < 8; ++j)
+    d = __builtin_amdgcn_mfma_f32_16x16x4f32(j < 4 ? w0[j & 3] : w1[j & 3], s.b[j], d, 0, 0, 0);
+  // lane l holds column l % 16 of lines 4 (l / 16) + i: row 4 (l / 16 % 2) + i, half l / 32
+  const int col = (lane & 15) - 3 * (lane >> 5);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int r = 4 * (row & 1) + i;   // (lane r's row)
+    const int er = __shfl(valid ? e : -1, r, 64);
+    if (col >= 0 && col < 3 && er >= 0) unsafeAtomicAdd(&sm.acc[er * kTerms + 6 + col], d[i]);
+  }
   if (__builtin_expect(special, 0)) {
 #pragma unroll 1
     for (int m = 0; m < kRowBlock; ++m) {
-      const float p = vbuf[m * kVStride + lane], wgt = vbuf[(kRowBlock + m) * kVStride + lane];
-      if (pb.bad && p != 0.0f) {
-        vbuf[m * kVStride + lane] = 0.0f;
-        direct_power_terms(J, sm.g[wl8[m]], fresh(px) + 0.5, fresh(py) + 0.5, p);
-      }
-      if (pb.bad && wgt != 0.0f) direct_colour_terms(J, sm.g[wl8[m]], wgt, pb.g0, pb.g1, pb.g2);
+      const float wm = vbuf[m * kVStride + lane];
+      const int em = __shfl(e, m, 64);
+      if (pb.bad && wm != 0.0f) direct_colour_terms(J, sm.g[em], wm, pb.g0, pb.g1, pb.g2);
     }
-    wave_fence();
-  }
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const float4v f = rp[q];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) d = __builtin_amdgcn_mfma_f32_16x16x4f32(f[e], s.b[4 * q + e], d, 0, 0, 0);
-  }
-  // lane l holds column l % 16 of lines 4 (l / 16) + i
-  const int col = lane & 15, r0 = 4 * ((lane >> 4) & 1);
-  const uint32_t four = *reinterpret_cast<const uint32_t *>(wl8 + r0);
-  if (lane < 32 ? col < 6 : (col >= 6 && col < kTerms)) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      if (r0 + i < rows) unsafeAtomicAdd(&sm.acc[((four >> (8 * i)) & 255u) * kTerms + col], d[i]);
   }
   wave_fence();   // the buffer is free for the next rows
 }
@@ -273,8 +294,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_raster_backward(BackwardJob J, in
   const float X = px + 0.5f, Y = py + 0.5f;
   const bool inside = (ox + px < J.W) && (oy + py < J.H);
 
-  float eu = 0.0f, ev = 0.0f;                              // this thread's staged entry
-  float4 eco = make_float4(0.0f, 0.0f, 0.0f, 1.0f);
+  float4 eco = make_float4(0.0f, 0.0f, 0.0f, 1.0f);        // this thread's staged entry
   auto stage = [&](uint32_t cs, int cnt) {
     if (t < cnt) {
       const uint32_t g = J.vals[cs + t];
@@ -285,8 +305,6 @@ __global__ __launch_bounds__(kBlock, 4) void k_raster_backward(BackwardJob J, in
       sm.b[t] = make_float4(-0.5f * kLog2e * co.z, __log2f(co.w), cl.x, cl.y);
       sm.c[t] = cl.z;
       sm.s.g[t] = g;
-      eu = (float)(m.x - ((double)ox + 8.0));
-      ev = (float)(m.y - ((double)oy + 8.0));
       eco = co;
       sm.s.qm[t] = all_rows ? (uint8_t)0xF
                             : (uint8_t)mfma::quad_mask((float)(m.x - ((double)ox + 8.5)),
@@ -386,6 +404,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_raster_backward(BackwardJob J, in
       const int sl = r0 + (lane & (kRowBlock - 1));
       const int idx = sl < n ? (int)sm.s.wl[w][sl] : kBlock;
       bool any = false;
+      float wgt[kRowBlock];
 #pragma unroll
       for (int k = kRowBlock - 4; k >= 0; k -= 4) {
         float D[4], cr[4], cg[4], cb[4];
@@ -402,19 +421,22 @@ __global__ __launch_bounds__(kBlock, 4) void k_raster_backward(BackwardJob J, in
         }
 #pragma unroll
         for (int j = 3; j >= 0; --j) {
-          float wgt = 0.0f, p = 0.0f;
+          float p = 0.0f;
+          wgt[k + j] = 0.0f;
           const bool act = ri[j] < lim && D[j] >= kCutLog2;
           any |= act;
-          if (act) back_step(pb, D[j], cr[j], cg[j], cb[j], &wgt, &p);
+          if (act) back_step(pb, D[j], cr[j], cg[j], cb[j], &wgt[k + j], &p);
           vbuf[(k + j) * kVStride + lane] = p;
-          vbuf[(kRowBlock + k + j) * kVStride + lane] = wgt;
         }
       }
-      if (__ballot(any) != 0)
-        add_row_sums(J, vbuf, side, sm.s.wl[w] + r0, n - r0, sm.s, pb, ox + px, oy + py, special);
+      if (__ballot(any) != 0) {
+        const float2 c = *reinterpret_cast<const float2 *>(&sm.a[idx]);
+        add_row_sums(J, vbuf, side, sm.s, idx, sl < n, c.x, c.y, (w & 1) * 8 + 0.5f, (w >> 1) * 8 + 0.5f, wgt, pb,
+                     special);
+      }
     }
     block_sync();
-    if (t < cnt) convert_sums(sm.s.acc + t * kTerms, eu, ev, eco);
+    if (t < cnt) convert_sums(sm.s.acc + t * kTerms, eco);
     block_sync();
     flush_entries(J, sm.s, cnt);
     if (cs == start) break;
@@ -437,6 +459,7 @@ struct BwdMfmaShared {
   static constexpr int RS = (S == 3) ? 32 : 16;
   __align__(16) uint16_t A[kBlock * RS];   // Gaussian-side rows
   float col[3][kBlock];                    // r, g, b
+  float2 uv[kBlock];                       // centre in the tile frame
   SumShared s;
 };
 
@@ -477,7 +500,6 @@ __global__ __launch_bounds__(kBlock, S == 3 ? 3 : 4) void k_raster_backward_mfma
   for (uint32_t ce = tile_last; ce > 0;) {
     const int cnt = (int)min((uint32_t)kBlock, ce);
     const uint32_t cs = ce - (uint32_t)cnt;   // positions in the tile's list
-    float eu = 0.0f, ev = 0.0f;
     float4 eco = make_float4(0.0f, 0.0f, 0.0f, 1.0f);
     block_sync();
     if (t < cnt) {
@@ -493,8 +515,7 @@ __global__ __launch_bounds__(kBlock, S == 3 ? 3 : 4) void k_raster_backward_mfma
       sm.col[2][t] = cl.z;
       sm.s.g[t] = g;
       sm.s.qm[t] = all_rows ? (uint8_t)0xF : (uint8_t)mfma::quad_mask(u, v, co.x, co.y, co.z, l2o);
-      eu = (float)(m.x - ((double)ox + 8.0));
-      ev = (float)(m.y - ((double)oy + 8.0));
+      sm.uv[t] = make_float2(u, v);
       eco = co;
     }
 #pragma unroll
@@ -531,22 +552,27 @@ __global__ __launch_bounds__(kBlock, S == 3 ? 3 : 4) void k_raster_backward_mfma
           D[4 + j] = __uint_as_float(pr[1]);
         }
         bool any = false;
+        float wgt[kRowBlock];
 #pragma unroll
         for (int m = kRowBlock - 1; m >= 0; --m) {
           const int ri = __builtin_amdgcn_readlane(rr, kRowBlock * r + m);   // (a slot past n: D = -1000)
-          float wgt = 0.0f, p = 0.0f;
+          float p = 0.0f;
+          wgt[m] = 0.0f;
           const bool act = ri < lim && D[m] >= kCutLog2;
           any |= act;
-          if (act) back_step(pb, D[m], sm.col[0][ri], sm.col[1][ri], sm.col[2][ri], &wgt, &p);
+          if (act) back_step(pb, D[m], sm.col[0][ri], sm.col[1][ri], sm.col[2][ri], &wgt[m], &p);
           vbuf[m * kVStride + lane] = p;
-          vbuf[(kRowBlock + m) * kVStride + lane] = wgt;
         }
-        if (__ballot(any) != 0)
-          add_row_sums(J, vbuf, side, sm.s.wl[w] + first, n - first, sm.s, pb, ox + px, oy + py, special);
+        if (__ballot(any) != 0) {
+          const int e = __shfl(rr, kRowBlock * r + (lane & (kRowBlock - 1)), 64);
+          const float2 c = sm.uv[e];
+          add_row_sums(J, vbuf, side, sm.s, e, first + (lane & (kRowBlock - 1)) < n, c.x, c.y, (w & 1) * 8 - 8.0f,
+                       (w >> 1) * 8 - 8.0f, wgt, pb, special);
+        }
       }
     }
     block_sync();
-    if (t < cnt) convert_sums(sm.s.acc + t * kTerms, eu, ev, eco);
+    if (t < cnt) convert_sums(sm.s.acc + t * kTerms, eco);
     block_sync();
     flush_entries(J, sm.s, cnt);
     ce = cs;
