@@ -88,8 +88,9 @@ enum {
   GS_OPT_TIGHT = 1u,
   /* The rasterizers and the backward passes leave out of each 8x8 quadrant's rows those whose alpha
    * cannot reach the 1/255 cut at any pixel centre of that quadrant (the test is taken with a
-   * margin of 1 in q, far above its own and the split operands' rounding, so the image and
-   * every aux plane are those of the full rows).  This flag makes every quadrant run every row
+   * margin of 1 in q, far above its own and the split operands' rounding, in FP32 with one that
+   * grows with the power's rounding over long thin splats, so the image and every aux plane are
+   * those of the full rows).  This flag makes every quadrant run every row
    * of its tile, the plain tile loop; it exists to check that equality and changes no result. */
   GS_OPT_ALL_ROWS = 2u,
   /* Grouped MFMA rasterization (group > 1).  By default 2x2 groups build each entry's

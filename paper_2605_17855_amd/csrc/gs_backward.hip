@@ -307,9 +307,9 @@ __global__ __launch_bounds__(kBlock, 4) void k_raster_backward(BackwardJob J, in
       sm.s.g[t] = g;
       eco = co;
       sm.s.qm[t] = all_rows ? (uint8_t)0xF
-                            : (uint8_t)mfma::quad_mask((float)(m.x - ((double)ox + 8.5)),
-                                                       (float)(m.y - ((double)oy + 8.5)), co.x, co.y, co.z,
-                                                       mfma::log2_opacity(co.w));
+                            : (uint8_t)mfma::quad_mask_fp32((float)(m.x - ((double)ox + 8.5)),
+                                                            (float)(m.y - ((double)oy + 8.5)), co.x, co.y, co.z,
+                                                            mfma::log2_opacity(co.w));
     }
   };
 

@@ -127,12 +127,12 @@ __device__ __forceinline__ void build_row(uint16_t *row, float u, float v, float
 constexpr float kQuadMargin = 1.0f;
 constexpr float kQuadQ0 = 11.0825270f + kQuadMargin;   // 2 ln 255 + margin
 
-__device__ __forceinline__ uint32_t quad_mask(float u, float v, float a, float b, float c, float l2o) {
+// The quadrants where q stays within Q somewhere; all of them for a conic that is not positive definite.
+__device__ __forceinline__ uint32_t quads_within(float u, float v, float a, float b, float c, float Q) {
 #pragma clang fp contract(off)
-  const float Q = fmaf(2.0f * kLn2, l2o, kQuadQ0);   // 2 ln(o) + 2 ln 255 + margin
-  if (!(Q > 0.0f)) return 0u;               // o < 1/255 e^{-margin/2}: never reaches the cut
   const float det = (float)((double)a * c - (double)b * b);
   if (!(a > 0.0f && c > 0.0f && det > 0.0f)) return 0xFu;
+  if (!(Q > 0.0f)) return 0u;
   const float ia = __builtin_amdgcn_rcpf(a), ic = __builtin_amdgcn_rcpf(c);
   const float ba = b * ia, bc = b * ic, ga = det * ia, gc = det * ic;
   uint32_t mask = 0;
@@ -156,6 +156,24 @@ __device__ __forceinline__ uint32_t quad_mask(float u, float v, float a, float b
     }
   }
   return mask;
+}
+
+__device__ __forceinline__ uint32_t quad_mask(float u, float v, float a, float b, float c, float l2o) {
+  const float Q = fmaf(2.0f * kLn2, l2o, kQuadQ0);   // 2 ln(o) + 2 ln 255 + margin
+  if (!(Q > 0.0f)) return 0u;               // o < 1/255 e^{-margin/2}: never reaches the cut
+  return quads_within(u, v, a, b, c, Q);
+}
+
+// The same for the FP32 power, D = log2(o) - (log2 e / 2)(a dx^2 + 2 b dx dy + c dy^2) from offsets of
+// the whole footprint.  Its terms come to at most S = a dx^2 + c dy^2 (in q) and cancel where a splat is long
+// and thin; with the rounding of the offsets and coefficients D is off by at most 18 x 2^-24 S in q (up
+// to 6.4 seen), which exceeds any fixed margin from a few thousand pixels on.  So Q grows by 32 x 2^-24 S,
+// S at the tile's pixel farthest from the centre: nothing for ordinary splats (S of some hundreds).
+constexpr float kFp32Slack = 0x1p-19f;
+__device__ __forceinline__ uint32_t quad_mask_fp32(float u, float v, float a, float b, float c, float l2o) {
+  const float dx = fabsf(u) + 8.0f, dy = fabsf(v) + 8.0f;
+  const float S = fmaf(a * dx, dx, c * dy * dy);
+  return quads_within(u, v, a, b, c, fmaf(kFp32Slack, S, fmaf(2.0f * kLn2, l2o, kQuadQ0)));
 }
 
 // Compacts, in order, the rows [0, nrows) whose quadrant mask holds this wave's bit into the

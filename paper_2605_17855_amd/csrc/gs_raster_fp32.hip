@@ -10,8 +10,8 @@
 // centre, so |d| stays small and exact.
 //
 // Each wave walks only the rows whose alpha can reach the 1/255 cut in its own quadrant (the
-// quadrant mask of the tensorized rasterizer, its margin far above this test's and the FP32
-// power's rounding, so no output changes).  A row's nine floats are LDS reads broadcast to 64
+// quadrant mask of the tensorized rasterizer, with a margin that follows the FP32 power's rounding,
+// so no output changes).  A row's nine floats are LDS reads broadcast to 64
 // pixels, ~20 LDS cycles per wave and row at 128 B per cycle, and four SIMDs share one LDS:
 // running every row in every quadrant was bound by exactly that (6.3M wave-rows of a 1M-Gaussian
 // 1080p frame, 242 us).  The lists keep about a third of them.
@@ -104,7 +104,7 @@ __device__ __forceinline__ void stage_row(SM &sm, int pos, double2 m, float4 co,
   sm.c[pos] = cl.z;
   const float ut = (float)(m.x - ((double)tx0 + 8.5)), vt = (float)(m.y - ((double)ty0 + 8.5));
   sm.qm[pos] = all_rows ? (uint8_t)0xF
-                        : (uint8_t)mfma::quad_mask(ut, vt, co.x, co.y, co.z, mfma::log2_opacity(co.w));
+                        : (uint8_t)mfma::quad_mask_fp32(ut, vt, co.x, co.y, co.z, mfma::log2_opacity(co.w));
 }
 
 template <bool AUX>
