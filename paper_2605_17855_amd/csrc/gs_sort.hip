@@ -873,28 +873,23 @@ struct BlockBinning {
 };
 constexpr uint32_t kEmptyDesc = 1u;   // x0 = 1, x1 = 1: no tile
 
-// Entry j of such a Gaussian: its j-th block, or false.  (Mostly small footprints over a block edge:
-// few blocks of few tile rows, so each is tested by its own rows.)
+// Entry j of such a Gaussian: its j-th block, or false.  A block row's blocks are those of a group row
+// of 8x8 groups, so each row costs its 8 spans, however many blocks it holds (tested block by block, the
+// long diagonal splats of a dense scene held their workgroups for longer than all others took).
 __device__ __forceinline__ bool culled_block(const BlockBinning &bb, uint32_t g, ushort4 r, uint32_t j, int *gx,
                                              int *gy) {
   const double2 m = bb.xy[g];
   const float4 co = bb.conic[g];
   const TightEllipse el = tight_ellipse(m.x, m.y, co.x, co.y, co.z, co.w, r.x, r.z - 1, r.y);
   for (int by = r.y / kBlockTiles; by <= (r.w - 1) / kBlockTiles; ++by) {
-    const int y0 = max((int)r.y, by * kBlockTiles), y1 = min((int)r.w, (by + 1) * kBlockTiles);
-    for (int bx = r.x / kBlockTiles; bx <= (r.z - 1) / kBlockTiles; ++bx) {
-      bool hit = false;
-      for (int y = y0; y < y1 && !hit; ++y) {
-        int lo, hi;
-        tight_row_span(el, y, &lo, &hi);
-        hit = lo <= hi && lo < (bx + 1) * kBlockTiles && hi >= bx * kBlockTiles;
-      }
-      if (hit && j-- == 0) {
-        *gx = bx;
-        *gy = by;
-        return true;
-      }
+    const TightGroupRow row = tight_group_row(el, kBlockTiles, by, r.w - 1);
+    const uint32_t n = tight_group_count(row);
+    if (j < n) {
+      *gx = tight_group_nth(row, j);
+      *gy = by;
+      return true;
     }
+    j -= n;
   }
   return false;
 }
