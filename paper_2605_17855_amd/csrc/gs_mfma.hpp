@@ -127,12 +127,11 @@ __device__ __forceinline__ void build_row(uint16_t *row, float u, float v, float
 constexpr float kQuadMargin = 1.0f;
 constexpr float kQuadQ0 = 11.0825270f + kQuadMargin;   // 2 ln 255 + margin
 
-// The quadrants where q stays within Q somewhere; all of them for a conic that is not positive definite.
+// The quadrants where q comes down to Q; all of them for a conic that is not positive definite.
 __device__ __forceinline__ uint32_t quads_within(float u, float v, float a, float b, float c, float Q) {
 #pragma clang fp contract(off)
   const float det = (float)((double)a * c - (double)b * b);
   if (!(a > 0.0f && c > 0.0f && det > 0.0f)) return 0xFu;
-  if (!(Q > 0.0f)) return 0u;
   const float ia = __builtin_amdgcn_rcpf(a), ic = __builtin_amdgcn_rcpf(c);
   const float ba = b * ia, bc = b * ic, ga = det * ia, gc = det * ic;
   uint32_t mask = 0;
