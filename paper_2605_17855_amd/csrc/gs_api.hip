@@ -233,17 +233,36 @@ bool poll_counts(volatile uint64_t *h, uint64_t *kv) {
   }
 }
 
-// Whether the bins are made by way of 8x8-tile blocks (bin_and_sort_blocks): where there are many
-// entries, and many tiles to sort them by (fewer take short radix passes anyway).  The entries'
-// number is not known yet; the capacity bounds it, and callers size it by the scene or by earlier
-// frames.  From 2^21 entries and 2^11 tiles the shorter sort pays for the expansion's kernels (direct
-// -> two-level, whole frames: 1M Gaussians at 1280x720 208 -> 196 us, at 2560x1440 302 -> 262;
-// 960x540, 2,040 tiles: 192 -> 197; 500K at 1280x720 equal).  Opacity-aware culling's masks gather the
-// Gaussians' records in block order, twice: from 2^22 and 2^13 (preparation only, 2M at 2560x1440 302 ->
-// 284 us; at 1920x1080, 8,160 tiles, 257 -> 273).
-bool two_level(const gsi::Grid &g, uint64_t capacity, bool tight) {
-  return g.G <= 4 && gsi::block_count(g) <= gsi::kMaxBlocks && gsi::bits_for((uint64_t)g.nbins) > 8 &&
-         g.TX * g.TY > (tight ? 1 << 13 : 1 << 11) && capacity > (tight ? 1ull << 22 : 1ull << 21);
+// For which frames the bins are made by way of 8x8-tile blocks (bin_and_sort_blocks): where there are
+// entries enough that the shorter sort pays for the expansion's kernels.  It goes by the frame's own
+// counts, which the host learns before the entries of a Gaussian are counted.  Bin sorts alone (depth
+// sort included), direct -> by blocks, over 480x270 to 3840x2160, 500 to 6M Gaussians and three kinds
+// of scene:
+//   two radix passes of bins (more than 512): level at 2^20 entries (954K at 3200x1800 98 -> 99 us,
+//     1,045K at 1920x1080 100 -> 95), then 133 -> 110 at 2M, 434 -> 247 at 10M;
+//   one pass of nine bits: where the blocks leave far fewer entries to sort (two entries per visible
+//     Gaussian 175 -> 188 us, six 107 -> 100, sixteen 127 -> 104); single tiles, at most 512 of them,
+//     not even then (2M entries 106 -> 113);
+//   culled single tiles: the masks gather the Gaussians' records in block order, twice (4.4 entries per
+//     Gaussian 331 -> 352 us, 4.8 200 -> 202, 5.4 373 -> 362, 6.7 231 -> 213, 13.7 804 -> 437);
+//   culled groups: the direct binning walks rows of groups (1,582K entries at 1600x900 4x4 352 -> 323 us,
+//     1,334K at 2240x1260 2x2 302 -> 193).
+constexpr uint64_t kBlockEntries = 1ull << 20;
+constexpr gsi::BlockRule kNoBlocks{~0ull, 0};
+gsi::BlockRule block_rule(const gsi::Grid &g, bool tight) {
+  if (g.G > 4 || gsi::block_count(g) > gsi::kMaxBlocks || g.nbins <= (g.G > 1 ? 256 : 512)) return kNoBlocks;
+  const uint64_t per_gaussian = tight ? (g.G == 1 ? 5 : 0) : (g.nbins <= 512 ? 4 : 0);
+  return gsi::BlockRule{kBlockEntries, per_gaussian};
+}
+
+// The same where the counts stay on the device: by the capacity, which callers size by the scene or by
+// earlier frames.  (Plain frames of few entries in a large capacity too: 50K Gaussians at 1080p with room
+// for 6M entries 84 -> 81 us, for 40M 96 -> 89; at 2160p, whose block pass takes nine bits, 86 -> 90.)
+gsi::BlockRule block_rule_device(const gsi::Grid &g, uint64_t capacity, bool tight) {
+  const gsi::BlockRule r = block_rule(g, tight);
+  const bool takes = r.entries != kNoBlocks.entries && g.nbins > 512 && g.TX * g.TY > (tight ? 1 << 13 : 1 << 11) &&
+                     capacity > (tight ? 1ull << 22 : 1ull << 21);
+  return takes ? gsi::BlockRule{0, 0} : kNoBlocks;
 }
 
 gs_status do_bin_sort(const gs_projected *proj, int64_t n, const gs_camera *cam, const gs_options *opt,
@@ -251,9 +270,10 @@ gs_status do_bin_sort(const gs_projected *proj, int64_t n, const gs_camera *cam,
   const gsi::Grid g = gsi::make_grid(cam->width, cam->height, opt->group);
   const Workspace w = carve(ws, n, bins->capacity);
   // The one host wait reads the entry count K and the visible count V, which k_depth_keys writes
-  // to the caller's pinned host memory (and to the workspace).  The depth sort (which reads V on
-  // the device and also places each Gaussian's first entry) is enqueued before the host polls
-  // for them, so the GPU keeps working while the host waits.
+  // to the caller's pinned host memory (and to the workspace).  The first three passes of the depth
+  // sort (which read V on the device) are enqueued before the host polls for them, so the GPU keeps
+  // working while the host waits; the last pass, which places each Gaussian's first entry, and
+  // the binning follow.
   // With the counts read on the device (GS_OPT_DEVICE_COUNTS) there is no host wait: the bin
   // sort's grids are sized for the capacity and its kernels take K (0 on overflow) and V from
   // the workspace.
@@ -262,9 +282,10 @@ gs_status do_bin_sort(const gs_projected *proj, int64_t n, const gs_camera *cam,
   if (hkv) hkv[0] = hkv[1] = ~0ull;   // overwritten by the kernel
   const uint64_t nn = (uint64_t)(n > 0 ? n : 1);
   const bool tight = (opt->flags & GS_OPT_TIGHT) != 0;
-  const bool blocks = nn > 1 && two_level(g, bins->capacity, tight);
-  const gsi::EntryCounts count{blocks && !tight ? nullptr : proj->count,
-                               blocks ? reinterpret_cast<const ushort4 *>(proj->rect) : nullptr};
+  const gsi::BlockRule rule = nn == 1 ? kNoBlocks
+                              : dev_counts ? block_rule_device(g, bins->capacity, tight) : block_rule(g, tight);
+  const gsi::EntryCounts by_bins{proj->count, nullptr};
+  const gsi::EntryCounts by_blocks{tight ? proj->count : nullptr, reinterpret_cast<const ushort4 *>(proj->rect)};
   const uint32_t *kclamp = reinterpret_cast<const uint32_t *>(w.counts + 2);   // K, or 0 above the capacity
   uint32_t *entries = reinterpret_cast<uint32_t *>(w.counts + 3);
   const float4 *rgb = reinterpret_cast<const float4 *>(proj->rgb);
@@ -272,27 +293,34 @@ gs_status do_bin_sort(const gs_projected *proj, int64_t n, const gs_camera *cam,
   const bool one = nn > 1 && gsi::depth_sort_one(nn);
   if (one)
     GS_HIP(gsi::launch_depth_sort_one(proj->order, rgb, proj->n_visible, w.dkey, proj->offset + n, w.counts, hcounts,
-                                      bins->capacity, count, w.dpos, w.bfirst, w.nbfirst, blocks ? entries : nullptr,
+                                      bins->capacity, by_bins, by_blocks, rule, w.dpos, w.bfirst, w.nbfirst, entries,
                                       st));
   else
     GS_HIP(gsi::launch_depth_keys(proj->order, rgb, proj->n_visible, nn, w.dkey, proj->offset + n, w.counts, hcounts,
                                   bins->capacity, w.sort, st));
   const uint32_t *dkeys = w.dkey;
   // from here on the kernel may be writing the counts: every exit waits for the stream first
-  // depth bits in depth order, and the first entry of each Gaussian in that order (a single
-  // Gaussian needs no sort: a gathered scan of its count; up to 8,192 are sorted already)
+  // depth bits in depth order (a single Gaussian needs no sort, up to 8,192 are sorted already)
   hipError_t e = hipSuccess;
-  if (nn == 1)
-    e = gsi::launch_scan_gather(proj->count, proj->order, w.dpos, (int64_t)nn, proj->n_visible, w.scan, st);
-  else if (!one)
-    e = gsi::sort_depth(proj->order, proj->n_visible, nn, w.dkey, w.dkey_alt, w.dval_alt, w.dval_b, w.sort, st, count,
-                        w.dpos, w.bfirst, w.nbfirst, blocks ? entries : nullptr, kclamp);
+  if (!one)
+    e = gsi::sort_depth_begin(proj->order, proj->n_visible, nn, w.dkey, w.dkey_alt, w.dval_alt, w.dval_b, w.sort, st);
   if (e != hipSuccess) {
     (void)hipStreamSynchronize(st);
     return hip_fail(e, "depth sort");
   }
-  // V and K: the counts, or upper bounds of *V_dev and *K_dev
-  auto bin = [&](uint32_t V, uint64_t K, const uint32_t *V_dev, const uint32_t *K_dev) {
+  // The first entry of each Gaussian in depth order (a gathered scan of a single one's count), then one
+  // thread per entry (also clears the bin ranges), the bin passes (the last one places the Gaussian
+  // indices and 64-bit keys), the ranges and masks.  V and K: the counts, or upper bounds of *V_dev and
+  // *K_dev.
+  auto bin = [&](bool blocks, uint32_t V, uint64_t K, const uint32_t *V_dev, const uint32_t *K_dev) {
+    hipError_t eb = hipSuccess;
+    if (nn == 1)
+      eb = gsi::launch_scan_gather(proj->count, proj->order, w.dpos, (int64_t)nn, proj->n_visible, w.scan, st);
+    else if (!one)
+      eb = gsi::sort_depth_end(proj->order, proj->n_visible, nn, w.dkey, w.dkey_alt, w.dval_alt, w.dval_b, w.sort, st,
+                               blocks ? by_blocks : by_bins, w.dpos, w.bfirst, w.nbfirst, blocks ? entries : nullptr,
+                               kclamp);
+    if (eb != hipSuccess) return eb;
     void *masks = opt->group > 1 ? bins->masks : nullptr;
     const uint32_t *firsts = nn > 1 ? w.bfirst : nullptr;
     if (blocks)
@@ -304,7 +332,7 @@ gs_status do_bin_sort(const gs_projected *proj, int64_t n, const gs_camera *cam,
                              bins->keys, w.sort, st);
   };
   if (dev_counts) {
-    GS_HIP(bin((uint32_t)nn, bins->capacity, proj->n_visible, kclamp));
+    GS_HIP(bin(rule.takes(bins->capacity, 0), (uint32_t)nn, bins->capacity, proj->n_visible, kclamp));
     return GS_OK;
   }
   uint64_t kv[2] = {0, 0};
@@ -318,9 +346,9 @@ gs_status do_bin_sort(const gs_projected *proj, int64_t n, const gs_camera *cam,
   const uint64_t K = kv[0];
   const uint32_t V = (uint32_t)kv[1];
   *n_keys = K;
-  // The depth sort and the depth-order scan enqueued above may still be writing the workspace
-  // and proj->order: an error return first waits for them, so that the caller may release or
-  // reuse the workspace (on any stream) as soon as the call returns.
+  // The depth passes enqueued above may still be writing the workspace and proj->order: an error return
+  // first waits for them, so that the caller may release or reuse the workspace (on any stream) as soon
+  // as the call returns.
   const char *why = nullptr;
   gs_status bad = GS_OK;
   if (K > bins->capacity) bad = GS_ERR_CAPACITY, why = "entries exceed capacity";
@@ -332,9 +360,7 @@ gs_status do_bin_sort(const gs_projected *proj, int64_t n, const gs_camera *cam,
     return fail(bad, "%s (%llu entries, capacity %llu, %u visible of %lld)", why, (unsigned long long)K,
                 (unsigned long long)bins->capacity, V, (long long)n);
   }
-  // one thread per entry (also clears the bin ranges), the bin passes (the last one places the
-  // Gaussian indices and 64-bit keys), the ranges and masks
-  GS_HIP(bin(V, K, nullptr, nullptr));
+  GS_HIP(bin(rule.takes(K, V), V, K, nullptr, nullptr));
   return GS_OK;
 }
 

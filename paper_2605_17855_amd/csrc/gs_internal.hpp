@@ -243,6 +243,14 @@ constexpr int kBlockTiles = 8;
 constexpr uint64_t kMaxBlocks = 512;   // one radix pass of at most 512 digits
 inline uint64_t block_count(const Grid &g) { return (uint64_t)make_grid(g.W, g.H, kBlockTiles).nbins; }
 
+// Frames whose bins are made by way of blocks: of at least `entries` entries, and `per_gaussian` of
+// them per visible Gaussian ({0, 0}: every frame, one without entries too).
+struct BlockRule {
+  uint64_t entries;
+  uint64_t per_gaussian;
+  __host__ __device__ bool takes(uint64_t K, uint64_t V) const { return K >= entries && K >= per_gaussian * V; }
+};
+
 // Entries of a Gaussian: count[g] (its bins), or with rect the 8x8-tile blocks its footprint
 // overlaps, with both the smaller of the two (opacity-aware culling can leave fewer bins than the
 // footprint has blocks; so the block entries fit wherever the bin entries do).
@@ -261,20 +269,24 @@ hipError_t launch_depth_keys(const uint32_t *order, const float4 *rgb, const uin
                              uint64_t capacity, void *tmp, hipStream_t st);
 // Sorts the visible list order[0..*nvis) stably by the depth keys in keys (four passes over
 // bits [0, 31): depths are positive), using keys_alt, vals_alt and vals_b (n_max each) as
-// scratch; the sorted depth keys end in keys.  The last pass also writes dpos[i] = the
-// entries of the Gaussians before the i-th in depth order (the exclusive scan of `count` of order[i],
-// dpos[*nvis] = all entries) and first[b] = the i whose entries hold entry b * kFirstsBlock, for
-// b < nfirst.  total (if set): all entries, at most *limit.  n_max > 1 (otherwise nothing is done).  Reads the visible count on the device,
-// so it can be enqueued before the host knows it.
-// launch_depth_keys and sort_depth in one launch, for scenes of up to 8,192 Gaussians (depth_sort_one).
+// scratch; the sorted depth keys end in keys.  In two parts, so that the host may learn the counts
+// between them: sort_depth_begin enqueues the first three passes, sort_depth_end the last, which also
+// writes dpos[i] = the entries of the Gaussians before the i-th in depth order (the exclusive scan of
+// `count` of order[i], dpos[*nvis] = all entries) and first[b] = the i whose entries hold entry
+// b * kFirstsBlock, for b < nfirst.  total (if set): all entries, at most *limit.  n_max > 1 (otherwise
+// nothing is done).  Reads the visible count on the device.
+hipError_t sort_depth_begin(uint32_t *order, const uint32_t *nvis, uint64_t n_max, uint32_t *keys, uint32_t *keys_alt,
+                            uint32_t *vals_alt, uint32_t *vals_b, void *tmp, hipStream_t st);
+hipError_t sort_depth_end(uint32_t *order, const uint32_t *nvis, uint64_t n_max, uint32_t *keys, uint32_t *keys_alt,
+                          uint32_t *vals_alt, uint32_t *vals_b, void *tmp, hipStream_t st, const EntryCounts &count,
+                          uint64_t *dpos, uint32_t *first, uint64_t nfirst, uint32_t *total, const uint32_t *limit);
+// launch_depth_keys and both parts in one launch, for scenes of up to 8,192 Gaussians (depth_sort_one).
+// Takes `blocks` for the entries where the rule takes the counts, else `bins` (and leaves total alone).
 bool depth_sort_one(uint64_t n_max);
 hipError_t launch_depth_sort_one(uint32_t *order, const float4 *rgb, const uint32_t *nvis, uint32_t *keys,
                                  const uint64_t *K, uint64_t *counts, uint64_t *host_counts, uint64_t capacity,
-                                 const EntryCounts &count, uint64_t *dpos, uint32_t *first, uint64_t nfirst,
-                                 uint32_t *total, hipStream_t st);
-hipError_t sort_depth(uint32_t *order, const uint32_t *nvis, uint64_t n_max, uint32_t *keys, uint32_t *keys_alt,
-                      uint32_t *vals_alt, uint32_t *vals_b, void *tmp, hipStream_t st, const EntryCounts &count,
-                      uint64_t *dpos, uint32_t *first, uint64_t nfirst, uint32_t *total, const uint32_t *limit);
+                                 const EntryCounts &bins, const EntryCounts &blocks, const BlockRule &rule,
+                                 uint64_t *dpos, uint32_t *first, uint64_t nfirst, uint32_t *total, hipStream_t st);
 // Entries of the V depth-ordered visible Gaussians (the i-th one's first entry at dpos[i];
 // dkeys[i] its depth bits) as (bin key, rank in depth order) pairs in (bkey, bval), a stable
 // sort on the bin bits ping-ponging with (bkey_alt, bval_alt) whose last pass writes the final
@@ -290,7 +302,7 @@ hipError_t bin_and_sort(const uint32_t *order, const uint32_t *dkeys, const uint
                         uint32_t *bkey, uint32_t *bval, uint32_t *bkey_alt, uint32_t *bval_alt, uint32_t *ranges,
                         void *masks, uint32_t *vals, uint64_t *keys, void *tmp, hipStream_t st);
 // The same bins by way of 8x8-tile blocks (block_count(g) <= kMaxBlocks, g.G <= 4): dpos and
-// block_first count block entries (sort_depth weighted by EntryCounts with rect), entries_dev their
+// block_first count block entries (sort_depth_end weighted by EntryCounts with rect), entries_dev their
 // number on the device (at most K); block_tmp holds block_tmp_bytes() bytes, tmp also
 // block_radix_tmp_bytes(K).
 hipError_t bin_and_sort_blocks(const uint32_t *order, const uint32_t *dkeys, const uint64_t *dpos,

@@ -622,7 +622,8 @@ __global__ __launch_bounds__(kOneThreads) void k_depth_sort_one(uint32_t *order,
                                                                 const uint32_t *nvis, uint32_t *keys,
                                                                 const uint64_t *K, uint64_t *counts,
                                                                 uint64_t *host_counts, uint64_t capacity,
-                                                                EntryCounts entries, FirstEntries fe) {
+                                                                EntryCounts bins, EntryCounts blocks, BlockRule rule,
+                                                                FirstEntries fe) {
   constexpr int kWaves = kOneThreads / 64;
   __shared__ uint32_t s_key[kOneKeys];
   __shared__ uint32_t s_val[kOneKeys];
@@ -630,6 +631,7 @@ __global__ __launch_bounds__(kOneThreads) void k_depth_sort_one(uint32_t *order,
   __shared__ uint32_t sh4[4];
   __shared__ uint64_t sh16[kWaves];
   __shared__ uint32_t s_and, s_or;
+  __shared__ bool s_blocks;
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const uint32_t n = *nvis;   // at most kOneKeys: the host's bound
   uint32_t limit = 0;
@@ -637,6 +639,7 @@ __global__ __launch_bounds__(kOneThreads) void k_depth_sort_one(uint32_t *order,
     s_and = ~0u;
     s_or = 0u;
     const uint64_t k = *K;
+    s_blocks = rule.takes(k, n);
     counts[0] = k;
     counts[1] = n;
     limit = k <= capacity ? (uint32_t)k : 0u;
@@ -747,6 +750,8 @@ __global__ __launch_bounds__(kOneThreads) void k_depth_sort_one(uint32_t *order,
     }
   }
   // keys and Gaussians out; the entries before each, over consecutive keys of each lane and round
+  const bool by_blocks = s_blocks;
+  const EntryCounts entries{by_blocks ? blocks.count : bins.count, by_blocks ? blocks.rect : nullptr};
   uint32_t ew[kOneR];
 #pragma unroll
   for (int r = 0; r < kOneR; ++r) {
@@ -790,7 +795,7 @@ __global__ __launch_bounds__(kOneThreads) void k_depth_sort_one(uint32_t *order,
   }
   if (t == 0) {
     fe.dpos[n] = wall;
-    if (fe.total) *fe.total = wall < (uint64_t)limit ? (uint32_t)wall : limit;
+    if (by_blocks) *fe.total = wall < (uint64_t)limit ? (uint32_t)wall : limit;
   }
 }
 
@@ -1255,7 +1260,7 @@ hipError_t radix_passes_r(KT *keys, uint32_t *vals, KT *keys_alt, uint32_t *vals
   uint32_t *vin = vals, *vout = vals_alt;
   const int width = DIG == kWideDigits ? kWideBits : pass_width(lo, hi);
   const FinalOut none{nullptr, nullptr, nullptr, nullptr};
-  const DigitWeights now{nullptr, {nullptr, nullptr}, nullptr, nullptr, nullptr, nullptr};
+  const DigitWeights now{};
   const FirstEntries nofe{nullptr, nullptr, 0, nullptr, nullptr};
   for (int shift = lo; shift < hi; shift += width) {
     const int bits = (hi - shift) < width ? (hi - shift) : width;
@@ -1340,8 +1345,9 @@ inline DepthTmp depth_tmp(void *tmp, uint64_t tiles) {
 
 // Keys ping-pong between keys and keys_alt; values run order -> vals_alt -> vals_b ->
 // vals_alt -> order, so that the sorted list ends where it started.
+// Passes [p0, p1).
 template <int R>
-hipError_t depth_passes(uint32_t *order, const uint32_t *nvis, uint64_t n_max, uint32_t *keys, uint32_t *keys_alt,
+hipError_t depth_passes(int p0, int p1, uint32_t *order, const uint32_t *nvis, uint64_t n_max, uint32_t *keys, uint32_t *keys_alt,
                         uint32_t *vals_alt, uint32_t *vals_b, void *tmp, hipStream_t st, const EntryCounts &count,
                         uint64_t *dpos, uint32_t *first, uint64_t nfirst, uint32_t *total, const uint32_t *limit) {
   const uint32_t tiles = (uint32_t)sort_tiles(n_max);
@@ -1349,7 +1355,7 @@ hipError_t depth_passes(uint32_t *order, const uint32_t *nvis, uint64_t n_max, u
   const unsigned grid = xcd_sort_grid(tiles);
   const uint32_t tile_keys = (uint32_t)SortTile<R>::kTile;
   const FinalOut none{nullptr, nullptr, nullptr, nullptr};
-  const DigitWeights now{nullptr, {nullptr, nullptr}, nullptr, nullptr, nullptr, nullptr};
+  const DigitWeights now{};
   const FirstEntries nofe{nullptr, nullptr, 0, nullptr, nullptr};
   uint32_t *kbuf[2] = {keys, keys_alt};
   uint32_t *vbuf[kDepthPasses + 1];
@@ -1360,7 +1366,7 @@ hipError_t depth_passes(uint32_t *order, const uint32_t *nvis, uint64_t n_max, u
   // (16-bit rows and their prefixes side by side in the room of the 32-bit counts)
   uint16_t *r16 = reinterpret_cast<uint16_t *>(d.counts);
   const dim3 groups((tiles + (1u << kRowShift) - 1u) >> kRowShift);
-  for (int p = 0; p < kDepthPasses; ++p) {
+  for (int p = p0; p < p1; ++p) {
     const int shift = p * kDepthWidth;
     uint32_t *kin = kbuf[p & 1], *kout = kbuf[(p + 1) & 1];
     if (p + 1 < kDepthPasses && in_rows) {
@@ -1432,22 +1438,28 @@ bool depth_sort_one(uint64_t n_max) { return n_max <= kOneKeys; }
 
 hipError_t launch_depth_sort_one(uint32_t *order, const float4 *rgb, const uint32_t *nvis, uint32_t *keys,
                                  const uint64_t *K, uint64_t *counts, uint64_t *host_counts, uint64_t capacity,
-                                 const EntryCounts &count, uint64_t *dpos, uint32_t *first, uint64_t nfirst,
-                                 uint32_t *total, hipStream_t st) {
+                                 const EntryCounts &bins, const EntryCounts &blocks, const BlockRule &rule,
+                                 uint64_t *dpos, uint32_t *first, uint64_t nfirst, uint32_t *total, hipStream_t st) {
   hipLaunchKernelGGL(k_depth_sort_one, dim3(1), dim3(kOneThreads), 0, st, order, rgb, nvis, keys, K, counts,
-                     host_counts, capacity, count, FirstEntries{dpos, first, nfirst, total, nullptr});
+                     host_counts, capacity, bins, blocks, rule, FirstEntries{dpos, first, nfirst, total, nullptr});
   return hipGetLastError();
 }
 
-hipError_t sort_depth(uint32_t *order, const uint32_t *nvis, uint64_t n_max, uint32_t *keys, uint32_t *keys_alt,
-                      uint32_t *vals_alt, uint32_t *vals_b, void *tmp, hipStream_t st, const EntryCounts &count,
-                      uint64_t *dpos, uint32_t *first, uint64_t nfirst, uint32_t *total, const uint32_t *limit) {
+hipError_t sort_depth_begin(uint32_t *order, const uint32_t *nvis, uint64_t n_max, uint32_t *keys, uint32_t *keys_alt,
+                            uint32_t *vals_alt, uint32_t *vals_b, void *tmp, hipStream_t st) {
   if (n_max <= 1) return hipSuccess;
-  if (n_max <= kSmallSort)
-    return depth_passes<kSmallR>(order, nvis, n_max, keys, keys_alt, vals_alt, vals_b, tmp, st, count, dpos, first,
-                                 nfirst, total, limit);
-  return depth_passes<kLargeR>(order, nvis, n_max, keys, keys_alt, vals_alt, vals_b, tmp, st, count, dpos, first,
-                               nfirst, total, limit);
+  auto passes = n_max <= kSmallSort ? depth_passes<kSmallR> : depth_passes<kLargeR>;
+  return passes(0, kDepthPasses - 1, order, nvis, n_max, keys, keys_alt, vals_alt, vals_b, tmp, st, EntryCounts{},
+                nullptr, nullptr, 0, nullptr, nullptr);
+}
+
+hipError_t sort_depth_end(uint32_t *order, const uint32_t *nvis, uint64_t n_max, uint32_t *keys, uint32_t *keys_alt,
+                          uint32_t *vals_alt, uint32_t *vals_b, void *tmp, hipStream_t st, const EntryCounts &count,
+                          uint64_t *dpos, uint32_t *first, uint64_t nfirst, uint32_t *total, const uint32_t *limit) {
+  if (n_max <= 1) return hipSuccess;
+  auto passes = n_max <= kSmallSort ? depth_passes<kSmallR> : depth_passes<kLargeR>;
+  return passes(kDepthPasses - 1, kDepthPasses, order, nvis, n_max, keys, keys_alt, vals_alt, vals_b, tmp, st, count,
+                dpos, first, nfirst, total, limit);
 }
 
 hipError_t bin_and_sort(const uint32_t *order, const uint32_t *dkeys, const uint64_t *dpos, const uint32_t *block_first,
@@ -1529,8 +1541,9 @@ hipError_t bin_and_sort_blocks(const uint32_t *order, const uint32_t *dkeys, con
   // (2,048-key tiles) at any length, so that its counts stay one per four keys.
   const int hi = bits_for((uint64_t)b.nbins);
   // (the block entries are a fifth to a tenth of the bin entries, so the larger sort tiles pay
-  // from four times as many of those)
-  const bool wide = hi > 8, large = wide || K > 4 * kSmallSort;
+  // from four times as many of those; where K is only a bound of them, from sixteen times: with a bound of
+  // 12M entries 88 us with larger tiles and 80 with smaller ones at 100K entries, 119 and 113 at 3M)
+  const bool wide = hi > 8, large = wide || K > (K_dev ? 16 : 4) * kSmallSort;
   const unsigned tiles = grid_for(K, large ? SortTile<kLargeR>::kTile : SortTile<kSmallR>::kTile);
   const unsigned grid = xcd_sort_grid(tiles);
   uint32_t *counts = static_cast<uint32_t *>(tmp);
@@ -1548,7 +1561,7 @@ hipError_t bin_and_sort_blocks(const uint32_t *order, const uint32_t *dkeys, con
     hipLaunchKernelGGL((k_binning<SortTile<kSmallR>::kTile>), dg, db, 0, st, order, dpos, block_first, V, K, V_dev,
                        entries_dev, r4, b.G, b.GX, hi, bkey, bval, ranges, nranges, fc, bb);
   const FinalOut none{nullptr, nullptr, nullptr, nullptr};
-  const DigitWeights now{nullptr, {nullptr, nullptr}, nullptr, nullptr, nullptr, nullptr};
+  const DigitWeights now{};
   const FirstEntries nofe{nullptr, nullptr, 0, nullptr, nullptr};
   hipLaunchKernelGGL(k_radix_digit_scan, dim3(1u << hi), db, 0, st, counts, tiles, totals, K, entries_dev,
                      (uint32_t)(large ? SortTile<kLargeR>::kTile : SortTile<kSmallR>::kTile), now);
