@@ -181,8 +181,16 @@ Workspace carve(void *ws, int64_t n, uint64_t capacity) {
 // per group left most CUs idle while the last, densest groups finished.  Every tile still
 // sees its rows in the same order with the same arithmetic, so the image does not depend on
 // the split.
-int raster_parts(const gs_options &o) {
-  if (o.precision != GS_PREC_FP32 && o.group == 2 && !(o.flags & GS_OPT_TILE_ROWS)) return 2;   // the group-frame rows
+// FP32, 2x2 groups: one workgroup per group again on large culled frames (raster_group_fp32).  Whether
+// the longest lists or the LDS reads of all rows bound a frame is the scene's; from 28 groups per
+// CU on the longest are hidden in any (per member tile -> per group: 3840x2160, 8,160 groups, clustered 1M
+// Gaussians 260 -> 271 us, 3M 472 -> 378, 50K 56 -> 31, dense 1M 535 -> 397; 2560x1440, 3,600 groups,
+// clustered 1M 150 -> 255, 3M 231 -> 272, dense 1M 255 -> 201).
+constexpr int64_t kWholeGroups = 7168;
+int raster_parts(const gs_options &o, int64_t groups) {
+  if (o.group == 2 && o.precision == GS_PREC_FP32)
+    return (o.flags & GS_OPT_TIGHT) && groups >= kWholeGroups ? 1 : 4;
+  if (o.group == 2 && !(o.flags & GS_OPT_TILE_ROWS)) return 2;   // the group-frame rows
   return o.group * o.group;
 }
 
@@ -372,17 +380,21 @@ gs_status batch_table(const gs_job *jobs, int32_t n_jobs, const gs_options *opt,
   if (n_jobs > gsi::kMaxBatch) return fail(GS_ERR_UNSUPPORTED, "n_jobs = %d above %d", n_jobs, gsi::kMaxBatch);
   if (n_jobs == 0) return GS_OK;
   if (!jobs) return fail(GS_ERR_INVALID_ARG, "jobs is NULL");
-  int64_t total = 0;
+  int64_t total = 0, groups = INT64_MAX;   // groups of the smallest image: one split for all jobs
+  for (int32_t i = 0; i < n_jobs; ++i) {
+    if ((s = check_camera(&jobs[i].cam))) return fail(s, "job %d: camera", i);
+    groups = std::min(groups, gsi::make_grid(jobs[i].cam.width, jobs[i].cam.height, opt->group).nbins);
+  }
+  const int parts = raster_parts(*opt, groups);
   for (int32_t i = 0; i < n_jobs; ++i) {
     const gs_job &jb = jobs[i];
-    if ((s = check_camera(&jb.cam))) return fail(s, "job %d: camera", i);
     if ((s = check_bins(jb.bins, opt->group, false))) return fail(s, "job %d: bins", i);
     if (!jb.proj || !jb.proj->xy || !jb.proj->conic || !jb.proj->rgb)
       return fail(GS_ERR_INVALID_ARG, "job %d: projected record is NULL", i);
     if (!jb.image) return fail(GS_ERR_INVALID_ARG, "job %d: image is NULL", i);
     if (opt->aux_flags && !jb.aux) return fail(GS_ERR_INVALID_ARG, "job %d: aux is NULL with aux_flags set", i);
     const gsi::Grid g = gsi::make_grid(jb.cam.width, jb.cam.height, opt->group);
-    table->jobs[i] = make_job(*jb.proj, *jb.bins, g, jb.image, jb.aux, raster_parts(*opt));
+    table->jobs[i] = make_job(*jb.proj, *jb.bins, g, jb.image, jb.aux, parts);
     table->jobs[i].bin0 = (int)total;
     total += table->jobs[i].items;
     if (total >= (1ll << 31)) return fail(GS_ERR_UNSUPPORTED, "batch has >= 2^31 work items");
@@ -555,7 +567,7 @@ gs_status gs_rasterize(const gs_projected *proj, const gs_bins *bins, const gs_c
   if (!image) return fail(GS_ERR_INVALID_ARG, "image is NULL");
   if (opt->aux_flags && !aux) return fail(GS_ERR_INVALID_ARG, "aux is NULL with aux_flags set");
   const gsi::Grid g = gsi::make_grid(cam->width, cam->height, opt->group);
-  const gsi::RasterJob j = make_job(*proj, *bins, g, image, aux, raster_parts(*opt));
+  const gsi::RasterJob j = make_job(*proj, *bins, g, image, aux, raster_parts(*opt, g.nbins));
   const gsi::RasterParams p = make_params(*opt);
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (opt->precision == GS_PREC_FP32)
@@ -608,7 +620,7 @@ gs_status gs_render(const gs_scene *scene, const gs_camera *cam, const gs_option
   GS_HIP(gsi::launch_preprocess(*scene, *cam, g, *proj, (opt->flags & GS_OPT_TIGHT) != 0, ws, st));
   GS_HIP(gsi::launch_scan_compact(proj->count, proj->offset, scene->n, proj->order, proj->n_visible, ws, true, st));
   if ((s = do_bin_sort(proj, scene->n, cam, opt, bins, n_keys, ws, st))) return s;
-  const gsi::RasterJob j = make_job(*proj, *bins, g, image, aux, raster_parts(*opt));
+  const gsi::RasterJob j = make_job(*proj, *bins, g, image, aux, raster_parts(*opt, g.nbins));
   const gsi::RasterParams p = make_params(*opt);
   if (opt->precision == GS_PREC_FP32)
     GS_HIP(gsi::launch_raster_fp32(j, p, st));
