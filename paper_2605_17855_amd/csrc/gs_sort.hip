@@ -684,7 +684,7 @@ __global__ __launch_bounds__(kOneThreads) void k_depth_sort_one(uint32_t *order,
   const uint32_t differ = s_and ^ s_or;
   for (int shift = 0; shift < kDepthBits; shift += 8) {
     if (((differ >> shift) & 0xffu) == 0u) continue;   // (uniform)
-    for (int i = t; i < kWaves * kDigits / 2; i += kOneThreads) reinterpret_cast<uint32_t *>(&wcnt[0][0])[i] = 0;
+    for (int d = lane; d < kDigits; d += 64) wcnt[w][d] = 0;
     block_sync();   // (and every wave has read its keys of the pass before)
 #pragma unroll
     for (int r = 0; r < kOneR; ++r) {
