@@ -46,3 +46,16 @@ def test_barriers_wait_for_lds_writes(source, tmp_path):
     asm = out.read_text()
     assert "s_barrier" in asm
     assert _unwaited(asm) == []
+
+
+@pytest.mark.parametrize("source", ["gs_sort.hip", "gs_preprocess.hip"])
+def test_barriers_of_sorts_and_scans_wait_for_lds_writes(source, tmp_path):
+    test_barriers_wait_for_lds_writes(source, tmp_path)
+
+
+def test_every_source_with_barriers_is_scanned():
+    scanned = {"gs_raster_fp32.hip", "gs_raster_mfma.hip", "gs_backward.hip", "gs_blocks.hip", "gs_sort.hip",
+               "gs_preprocess.hip"}
+    for source in build.SOURCES:
+        with open(os.path.join(build.CSRC, source)) as f:
+            assert source in scanned or not re.search(r"block_sync|__syncthreads", f.read()), source
