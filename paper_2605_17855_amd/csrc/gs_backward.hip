@@ -23,6 +23,11 @@
 // gradients and adds them with hardware FP32 atomics, once per (entry, tile).  Wave sums of every row
 // by lane swaps and DPP took ~45 vector instructions per row and one nine-lane global atomic per
 // (row, quadrant).
+//
+// What bounds it: vector issue (67 % of the SIMD cycles in FP32, 52 % in the MFMA variant) and LDS (61 and
+// 63 %) together, and the waves of unequal lists that meet at the chunk barriers.  One buffer for p and then
+// alpha T, instead of one each, brings the FP32 kernel from 38 to 29.5 KB: five workgroups per CU instead of
+// four.  1M Gaussians at 1920x1080: FP32 438 -> 400 us, FP16 327 -> 324 us, with all sums as moments before.
 #include "gs_backward.hpp"
 #include "gs_mfma.hpp"
 
