@@ -49,7 +49,7 @@ POWER_FLOPS = 12                    # the power's 6 multiply-adds, moved onto th
 # (SQ_INSTS_VALU) and the SIMD cycles spent on VALU instructions (SQ_ACTIVE_INST_VALU, in units
 # of 4 cycles, summed over the SIMDs).  They describe the kernel built from the source and
 # compiler flags hashed in `sha256`; after any change to either they are reported as null.
-RASTER_COUNTERS = dict(sha256="32b05e72c6e84ef62e43257b059be2794b5d3d248088fc74cf63084973edcb0a",
+RASTER_COUNTERS = dict(sha256="a0ec40910f7456fa7398e7fae21a7eef4ee35dc1deeb2ab61127fc7de1c608c2",
                        fetch_kib=65231, write_kib=25066, fetch_scale=2.0, write_scale=1.0,
                        insts_valu=34.77e6, active_valu_quads=38.46e6,
                        precision="fp16", splits=2, group=1, scene="clustered1m")

@@ -231,7 +231,7 @@ constexpr uint64_t kFirstsBlock = 1024;
 // ---- binning, sort, ranges -------------------------------------------------
 // scratch of a radix sort over at most n keys (per-tile digit counts and digit totals)
 size_t radix_tmp_bytes(uint64_t n);
-// scratch of the depth sort of n_max keys (sort_depth; counts, totals and the last pass's weights)
+// scratch of the depth sort of n_max keys (sort_depth_begin; counts, totals and the last pass's weights)
 size_t depth_sort_tmp_bytes(uint64_t n_max);
 // Stable sort of (keys, vals) on key bits [lo, hi); ping-pongs with (keys_alt, vals_alt) and
 // reports in *in_alt whether the result ended in the alternate buffers.
@@ -262,7 +262,7 @@ struct EntryCounts {
 // keys[i] = depth bits of order[i] for i < *nvis (n_max >= *nvis), counts = {*K, *nvis} (the
 // entry and visible counts side by side, for one copy to the host), the low 32 bits of counts[2]
 // = *K if *K <= capacity else 0 (the entry count the device-count bin sort takes), and in tmp
-// the first depth pass's per-tile digit counts for the sort_depth call that follows (same n_max
+// the first depth pass's per-tile digit counts for the sort_depth_begin call that follows (same n_max
 // and tmp).
 hipError_t launch_depth_keys(const uint32_t *order, const float4 *rgb, const uint32_t *nvis, uint64_t n_max,
                              uint32_t *keys, const uint64_t *K, uint64_t *counts, uint64_t *host_counts,
@@ -293,7 +293,7 @@ hipError_t launch_depth_sort_one(uint32_t *order, const float4 *rgb, const uint3
 // Gaussian indices to vals and the 64-bit keys to keys, then the bin ranges (cleared first) and,
 // for group > 1, the membership masks.  With tight (opacity-aware culling) entries follow the
 // culled spans of tight_row_span.  vals and keys must not alias the four work arrays.
-// block_first (or nullptr): the first Gaussian of every 1,024-entry block (sort_depth).
+// block_first (or nullptr): the first Gaussian of every 1,024-entry block (sort_depth_end).
 // V_dev and K_dev (both or neither): the visible and entry counts read on the device, V and K
 // then upper bounds of them (grids sized for K; the surplus workgroups return at once).
 hipError_t bin_and_sort(const uint32_t *order, const uint32_t *dkeys, const uint64_t *dpos, const uint32_t *block_first,

@@ -229,10 +229,11 @@ __device__ __forceinline__ uint32_t preprocess_one(const PreArgs &a, int64_t g) 
   return cnt;
 }
 
-// Bound by memory: a wave's lanes are neighbours in each of the 59 arrays, and any visible lane has
-// its lines read, so most of the scene's bytes move (6M Gaussians: 235 us, 6.0 TB/s).  Culling first and
-// running the visible ones compacted read no fewer lines (262 us), and so did larger workgroups or
-// several blocks in turn (2M Gaussians, 63 us: 78 to 90).
+// Bound by memory: 44 bytes of every Gaussian, streamed, and the 192 bytes of SH of each visible one, lines
+// scattered over the coefficients (6M Gaussians, dense scene: 572 MB read and 181 written in 203 to 235 us, 3.2
+// to 3.7 TB/s; 1M at 1080p 113 MB in 24 us, 4.7).  Culling first and running the visible ones compacted read
+// no fewer lines (262 us at 6M), and larger workgroups or several blocks in turn were slower too (2M
+// Gaussians, 63 us: 78 to 90).
 template <int DEG>
 __global__ __launch_bounds__(kBlock) void k_preprocess(PreArgs a) {
   __shared__ uint64_t sh[4];

@@ -1420,7 +1420,7 @@ size_t depth_sort_tmp_bytes(uint64_t n) { return depth_tmp(nullptr, sort_tiles(n
 hipError_t launch_depth_keys(const uint32_t *order, const float4 *rgb, const uint32_t *nvis, uint64_t n_max,
                              uint32_t *keys, const uint64_t *K, uint64_t *counts, uint64_t *host_counts,
                              uint64_t capacity, void *tmp, hipStream_t st) {
-  // one workgroup per tile of the depth sort that follows (sort_depth, same n_max): its first
+  // one workgroup per tile of the depth sort that follows (sort_depth_begin, same n_max): its first
   // pass's digit counts are taken here
   const uint32_t tiles = (uint32_t)sort_tiles(n_max ? n_max : 1);
   uint32_t *dcounts = depth_tmp(tmp, tiles).counts;
